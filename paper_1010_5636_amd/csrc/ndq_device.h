@@ -173,6 +173,11 @@ template <> struct SpinorIO<P32> {
         reinterpret_cast<float2*>(v.base)[2 * ((int64_t)(c >> 1) * v.stride + s) + (c & 1)] = make_float2(x.r, x.i);
     }
     // components 2j and 2j+1 (the whole 16-byte word of plane j)
+    __device__ static __forceinline__ void load_plane(const SpinorView& v, int64_t s, int j, C<R>& x, C<R>& y) {
+        const float4 w = reinterpret_cast<const float4*>(v.base)[(int64_t)j * v.stride + s];
+        x = {w.x, w.y};
+        y = {w.z, w.w};
+    }
     __device__ static __forceinline__ void store_plane(const SpinorView& v, int64_t s, int j, C<R> x, C<R> y) {
         reinterpret_cast<float4*>(v.base)[(int64_t)j * v.stride + s] = make_float4(x.r, x.i, y.r, y.i);
     }

@@ -125,11 +125,17 @@ __device__ __forceinline__ void hop_bwd(const C<R> s[12], const C<R> u[3][3], C<
     }
 }
 
+struct NoLoads {
+    __device__ __forceinline__ void operator()() const {}
+};
+
 // PAIR64: FP64 also issues both hops' loads together (the direction split with
 // 12- or 8-real links, where the registers this takes keep 3 wavefronts per SIMD).
-template <int SP, int LP, int RECON, int MU, bool NT, bool PAIR64 = false>
+// `more` issues further loads behind those of the hops, before their arithmetic.
+template <int SP, int LP, int RECON, int MU, bool NT, bool PAIR64 = false, typename More = NoLoads>
 __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, const int32_t nb[8],
-                                         const SpinorView& vin, C<typename SpinorIO<SP>::R> acc[12]) {
+                                         const SpinorView& vin, C<typename SpinorIO<SP>::R> acc[12],
+                                         More more = More()) {
     using R = typename SpinorIO<SP>::R;
     using F = LinkFmt<LP, RECON>;
     C<R> sf[12], sb[12];
@@ -142,6 +148,7 @@ __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, 
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, p * 4 + MU, i, wf);
         SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, (1 - p) * 4 + MU, nb[4 + MU], wb);
+        more();
         __builtin_amdgcn_sched_barrier(0);   // keep the arithmetic below every load
         link_decode<LP, RECON>(wf, u);
         hop_fwd<MU>(sf, u, acc);
@@ -154,6 +161,7 @@ __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, 
         hop_fwd<MU>(sf, u, acc);
         SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, (1 - p) * 4 + MU, nb[4 + MU], wb);
+        more();
         link_decode<LP, RECON>(wb, u);
         hop_bwd<MU>(sb, u, acc);
     }
@@ -269,16 +277,66 @@ __global__ void __launch_bounds__(BLOCK) k_wilson(WilsonArgs a) {
     }
 }
 
+// Epilogue of the direction split: the part of the 64 outputs that wavefront w
+// finishes, kN complex components from first(w).  F64: one spin component of
+// each site; F32: the two 16-byte planes 2w, 2w+1 (wavefronts 0..2), so that
+// every access is a full word; F16: the whole spinor (wavefront 0), because the
+// per-site scale needs all 24 reals.
+template <int SP> struct SplitPart;
+template <> struct SplitPart<P64> {
+    static constexpr int kN = 3;
+    __device__ static __forceinline__ bool has(int) { return true; }
+    __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, int w, C<double> x[kN]) {
+#pragma unroll
+        for (int k = 0; k < kN; ++k) x[k] = SpinorIO<P64>::load_comp(v, s, kN * w + k);
+    }
+    __device__ static __forceinline__ void store(const SpinorView& v, int64_t s, int w, const C<double> x[kN]) {
+#pragma unroll
+        for (int k = 0; k < kN; ++k) SpinorIO<P64>::store_comp(v, s, kN * w + k, x[k]);
+    }
+};
+template <> struct SplitPart<P32> {
+    static constexpr int kN = 4;
+    __device__ static __forceinline__ bool has(int w) { return w < 3; }
+    __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, int w, C<float> x[kN]) {
+        SpinorIO<P32>::load_plane(v, s, 2 * w, x[0], x[1]);
+        SpinorIO<P32>::load_plane(v, s, 2 * w + 1, x[2], x[3]);
+    }
+    __device__ static __forceinline__ void store(const SpinorView& v, int64_t s, int w, const C<float> x[kN]) {
+        SpinorIO<P32>::store_plane(v, s, 2 * w, x[0], x[1]);
+        SpinorIO<P32>::store_plane(v, s, 2 * w + 1, x[2], x[3]);
+    }
+};
+template <> struct SplitPart<P16> {
+    static constexpr int kN = 12;
+    __device__ static __forceinline__ bool has(int w) { return w == 0; }
+    __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, int, C<float> x[kN]) {
+        SpinorIO<P16>::load(v, s, x);
+    }
+    __device__ static __forceinline__ void store(const SpinorView& v, int64_t s, int, const C<float> x[kN]) {
+        SpinorIO<P16>::store(v, s, x);
+    }
+};
+
 // Direction-split variant for small lattices, where one lane per site leaves
 // most SIMDs with a single wavefront: a workgroup of 4 wavefronts covers 64
 // sites and wavefront w computes the two hops +-mu with mu = w (the direction is
 // uniform per wavefront, so there is no divergence).  The four partial sums
-// meet in LDS and are added in a fixed order; wavefront w then finishes spin
-// component w of the 64 outputs.  For F16 outputs wavefront 0 finishes the
-// whole spinor, because the per-site scale needs all 24 reals.
-template <int SP, int LP, int RECON, bool NT>
+// meet in LDS and are added in a fixed order; wavefront w then finishes its
+// part of the 64 outputs (SplitPart).
+//
+// Bound by memory round trips, on small lattices entirely.  The same-site
+// spinor and the up to NV = 3 extra vectors of the epilogue are therefore
+// loaded together with the hops' spinors and links, not after the barrier one
+// round trip each: one F32 sign apply on 24^3x48 14.2 -> 12.2 ms, the F32 Q
+// there 75.0 -> 70.6 us, a mixed solve on 8^3x16 381-420 -> 332-360 ms (loads
+// between the arithmetic and the barrier instead: 12.4 ms, 72.1 us and
+// 349-389 ms, although that keeps 5 wavefronts per SIMD instead of 4).  NV = 0
+// serves launches without extra vectors, whose registers the loads would cost.
+template <int SP, int LP, int RECON, bool NT, int NV>
 __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     using R = typename SpinorIO<SP>::R;
+    using Part = SplitPart<SP>;
     __shared__ C<R> part[4][12][64];
     __shared__ double red_lds[4];
     unsigned lin = blockIdx.y * gridDim.x + blockIdx.x;
@@ -286,10 +344,19 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     int y;
     const int32_t pos = parity_slot(lin, y);
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t i = order_tile(pos, (int32_t)gridDim.x, a.g.n0, a.order_c) * 64 + lane;
     const int p = a.p0 + y;
     const bool active = i < a.g.vh;
+    C<R> sf[Part::kN], vv[NV > 0 ? NV : 1][Part::kN];
+    // the epilogue's operands, in flight with those of the hops
+    auto epilogue_loads = [&]() {
+        if (!Part::has(w)) return;
+        if (a.has_self) Part::load(a.self[y], (int64_t)a.self[y].site0 + i, w, sf);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (j < a.nv) Part::load(a.v[j][y], (int64_t)a.v[j][y].site0 + i, w, vv[j]);
+    };
     if (active) {
         const SiteCoord x = eo_coords(a.g, p, i);
         int32_t nb[8];
@@ -299,108 +366,45 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
         for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
         const SpinorView& vin = a.in[y];
         switch (w) {
-            case 0: hop_pair<SP, LP, RECON, 0, NT, RECON != 18>(a, p, i, nb, vin, acc); break;
-            case 1: hop_pair<SP, LP, RECON, 1, NT, RECON != 18>(a, p, i, nb, vin, acc); break;
-            case 2: hop_pair<SP, LP, RECON, 2, NT, RECON != 18>(a, p, i, nb, vin, acc); break;
-            default: hop_pair<SP, LP, RECON, 3, NT, RECON != 18>(a, p, i, nb, vin, acc); break;
+            case 0: hop_pair<SP, LP, RECON, 0, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
+            case 1: hop_pair<SP, LP, RECON, 1, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
+            case 2: hop_pair<SP, LP, RECON, 2, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
+            default: hop_pair<SP, LP, RECON, 3, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
         }
 #pragma unroll
         for (int k = 0; k < 12; ++k) part[w][k][lane] = acc[k];
     }
     __syncthreads();
     double red = 0.0;
-    if (active) {
+    if (active && Part::has(w)) {
         const R b = (R)a.b_hop;
         const R as = (R)a.a_self;
         const R c0 = (R)coef(a.c0);
-        if constexpr (SP == P16) {
-            if (w == 0) {
-                C<R> t[12];
+        const int c1 = Part::kN * w;   // first component of this part
+        C<R> t[Part::kN];
 #pragma unroll
-                for (int k = 0; k < 12; ++k)
-                    t[k] = cadd(cadd(part[0][k][lane], part[1][k][lane]), cadd(part[2][k][lane], part[3][k][lane]));
-                if (a.has_self) {
-                    C<R> sf[12];
-                    SpinorIO<SP>::load(a.self[y], (int64_t)a.self[y].site0 + i, sf);
+        for (int k = 0; k < Part::kN; ++k) {
+            const int c = c1 + k;
+            t[k] = cadd(cadd(part[0][c][lane], part[1][c][lane]), cadd(part[2][c][lane], part[3][c][lane]));
+            if (a.has_self) t[k] = {as * sf[k].r + b * t[k].r, as * sf[k].i + b * t[k].i};
+            else t[k] = cscale(b, t[k]);
+            if (a.gamma5 && c >= 6) t[k] = cneg(t[k]);
+            t[k] = cscale(c0, t[k]);
+        }
 #pragma unroll
-                    for (int k = 0; k < 12; ++k) t[k] = {as * sf[k].r + b * t[k].r, as * sf[k].i + b * t[k].i};
-                } else {
+        for (int j = 0; j < NV; ++j) {
+            if (j < a.nv) {
+                const R cj = (R)coef(a.cv[j]);
 #pragma unroll
-                    for (int k = 0; k < 12; ++k) t[k] = cscale(b, t[k]);
-                }
-                if (a.gamma5) {
-#pragma unroll
-                    for (int k = 6; k < 12; ++k) t[k] = cneg(t[k]);
-                }
-#pragma unroll
-                for (int k = 0; k < 12; ++k) t[k] = cscale(c0, t[k]);
-                for (int j = 0; j < a.nv; ++j) {
-                    C<R> vv[12];
-                    SpinorIO<SP>::load(a.v[j][y], (int64_t)a.v[j][y].site0 + i, vv);
-                    const R cj = (R)coef(a.cv[j]);
-#pragma unroll
-                    for (int k = 0; k < 12; ++k) t[k] = {t[k].r + cj * vv[k].r, t[k].i + cj * vv[k].i};
-                }
-                SpinorIO<SP>::store(a.out[y], (int64_t)a.out[y].site0 + i, t);
-                if (a.partials) {
-                    SpinorIO<SP>::load(a.out[y], (int64_t)a.out[y].site0 + i, t);
-#pragma unroll
-                    for (int k = 0; k < 12; ++k) red += (double)t[k].r * t[k].r + (double)t[k].i * t[k].i;
-                }
+                for (int k = 0; k < Part::kN; ++k) t[k] = {t[k].r + cj * vv[j][k].r, t[k].i + cj * vv[j][k].i};
             }
-        } else {
-            const int64_t so = (int64_t)a.out[y].site0 + i;
-            if constexpr (SP == P32) {
-                // wavefronts 0..2 finish the two 16-byte planes 2w, 2w+1 each
-                // (components 4w..4w+3), so that every store is a full word
-                if (w < 3) {
-                    C<R> t4[4];
+        }
+        const int64_t so = (int64_t)a.out[y].site0 + i;
+        Part::store(a.out[y], so, w, t);
+        if (a.partials) {
+            if constexpr (SP == P16) Part::load(a.out[y], so, w, t);   // norm of what was stored (after F16 rounding)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int c = 4 * w + k;
-                        C<R> t = cadd(cadd(part[0][c][lane], part[1][c][lane]),
-                                      cadd(part[2][c][lane], part[3][c][lane]));
-                        if (a.has_self) {
-                            const C<R> sf = SpinorIO<SP>::load_comp(a.self[y], (int64_t)a.self[y].site0 + i, c);
-                            t = {as * sf.r + b * t.r, as * sf.i + b * t.i};
-                        } else {
-                            t = cscale(b, t);
-                        }
-                        if (a.gamma5 && c >= 6) t = cneg(t);
-                        t = cscale(c0, t);
-                        for (int j = 0; j < a.nv; ++j) {
-                            const C<R> vv = SpinorIO<SP>::load_comp(a.v[j][y], (int64_t)a.v[j][y].site0 + i, c);
-                            const R cj = (R)coef(a.cv[j]);
-                            t = {t.r + cj * vv.r, t.i + cj * vv.i};
-                        }
-                        t4[k] = t;
-                        red += (double)t.r * t.r + (double)t.i * t.i;
-                    }
-                    SpinorIO<SP>::store_plane(a.out[y], so, 2 * w, t4[0], t4[1]);
-                    SpinorIO<SP>::store_plane(a.out[y], so, 2 * w + 1, t4[2], t4[3]);
-                }
-            } else {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const int c = 3 * w + k;
-                C<R> t = cadd(cadd(part[0][c][lane], part[1][c][lane]), cadd(part[2][c][lane], part[3][c][lane]));
-                if (a.has_self) {
-                    const C<R> sf = SpinorIO<SP>::load_comp(a.self[y], (int64_t)a.self[y].site0 + i, c);
-                    t = {as * sf.r + b * t.r, as * sf.i + b * t.i};
-                } else {
-                    t = cscale(b, t);
-                }
-                if (a.gamma5 && w >= 2) t = cneg(t);
-                t = cscale(c0, t);
-                for (int j = 0; j < a.nv; ++j) {
-                    const C<R> vv = SpinorIO<SP>::load_comp(a.v[j][y], (int64_t)a.v[j][y].site0 + i, c);
-                    const R cj = (R)coef(a.cv[j]);
-                    t = {t.r + cj * vv.r, t.i + cj * vv.i};
-                }
-                SpinorIO<SP>::store_comp(a.out[y], so, c, t);
-                red += (double)t.r * t.r + (double)t.i * t.i;
-            }
-            }
+            for (int k = 0; k < Part::kN; ++k) red += (double)t[k].r * t[k].r + (double)t[k].i * t[k].i;
         }
     }
     if (a.partials) {
@@ -707,7 +711,15 @@ hipError_t launch_nt(const WilsonArgs& a, int ny, int block, hipStream_t st) {
     if (block == 0) {
         // direction split: 64 sites per workgroup of 4 wavefronts
         const dim3 grid((unsigned)((a.g.vh + 63) / 64), ny);
-        hipLaunchKernelGGL((k_wilson_dirsplit<SP, LP, RECON, NT>), grid, dim3(256), 0, st, a);
+        if constexpr (!NT) {
+            if (a.nv > 0) {
+                hipLaunchKernelGGL((k_wilson_dirsplit<SP, LP, RECON, NT, 3>), grid, dim3(256), 0, st, a);
+                return hipGetLastError();
+            }
+        } else if (a.nv > 0) {
+            return launch_nt<SP, LP, RECON, false>(a, ny, block, st);   // extra vectors: one instance per format
+        }
+        hipLaunchKernelGGL((k_wilson_dirsplit<SP, LP, RECON, NT, 0>), grid, dim3(256), 0, st, a);
         return hipGetLastError();
     }
     const unsigned nbx = (unsigned)((a.g.vh + block - 1) / block);
