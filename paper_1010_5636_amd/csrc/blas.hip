@@ -477,83 +477,143 @@ __global__ void __launch_bounds__(kBlock) k_phase_copy(SpinorView src, SpinorVie
 }
 
 // ---------------------------------------------------------------------------
-// Gram matrix of two blocks of FP64 full spinor fields on the matrix cores:
+// Gram matrix of two blocks of full spinor fields on the matrix cores:
 //   G[i][j] = <A_i, B_j> = sum over sites and the 12 components of conj(A_i) B_j,
-// a tall-skinny product (K = 12 V, at most 64 x 64 outputs).  One wavefront
-// accumulates a 16-row tile of G against up to four 16-column tiles over a
-// contiguous range of sites with v_mfma_f64_16x16x4f64: lane l supplies
-// A_{16 ti + l%16} and B_{16 tj + l%16} at site s + l/16, so each instruction
-// adds four sites' products; real and imaginary parts take four real products
-// (ar br + ai bi, ar bi - ai br).  The accumulator lane l, element r holds
-// row 4r + l/16, column l%16.  Per-wavefront partial tiles are summed in a
-// fixed order by k_gram_reduce.
+// a tall-skinny product (K = 12 V, at most 64 x 64 outputs), A in FP64, B in
+// F64, F32 or F16 (PB; converted to FP64).
+//
+// A workgroup takes one chunk of sites and stages K elements (G components of
+// S = K / G sites, G the components in a 16-byte word of B) of every row of A
+// and B in LDS, so that each field is read once and in runs of 16 S bytes; the
+// next stage is in flight in registers meanwhile.  A wavefront accumulates one
+// 16-row tile of G against up to NTJ 16-column tiles with
+// v_mfma_f64_16x16x4f64: lane l supplies A_{16 ti + l%16} and B_{16 tj + l%16}
+// at element e + l/16, so each instruction adds four elements' products; real
+// and imaginary parts take four real products (ar br + ai bi, ar bi - ai br).
+// Fewer than 3 row tiles leave wavefronts over: kp of them then share a row
+// tile, each with its part of the stage and its own partial tile.  The
+// accumulator lane l, element r holds row 4r + l/16, column l%16.  Partial tiles
+// are summed in a fixed order by k_gram_reduce.  Rows of a tile past na or nb
+// read another row's elements; only outputs nobody reads come of them.
+//
+// Bound by the FP64 matrix cores for large blocks and by HBM for small ones.
+// Measured, 60 x 60 FP64 fields on 24^3x48 (15.3 GB, 229 Gflop): 11.9 ms when
+// every wavefront loaded its operands from memory itself (16 fields x 64 bytes
+// per instruction, each field once per row tile through L1), 6.0 ms here.
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Component c of field `base` (precision PB, full-field layout with plane stride V) in FP64.
-template <int PB>
-__device__ __forceinline__ double2 field_comp(const char* base, int32_t V, int c, int32_t site) {
-    SpinorView v;
-    v.base = const_cast<char*>(base);
-    v.stride = V;
-    v.site0 = 0;
-    v.rhs_bytes = 0;
-    const auto x = SpinorIO<PB>::load_comp(v, site, c);
-    return make_double2((double)x.r, (double)x.i);
+// FP64 value of the g-th complex component in a 16-byte word of a packed field.
+template <int P>
+__device__ __forceinline__ double2 word_comp(const uint4& w, float scale, int g) {
+    if constexpr (P == P64) {
+        return make_double2(__hiloint2double((int)w.y, (int)w.x), __hiloint2double((int)w.w, (int)w.z));
+    } else if constexpr (P == P32) {
+        return g == 0 ? make_double2(__uint_as_float(w.x), __uint_as_float(w.y))
+                      : make_double2(__uint_as_float(w.z), __uint_as_float(w.w));
+    } else {
+        const uint32_t h = g == 0 ? w.x : g == 1 ? w.y : g == 2 ? w.z : w.w;
+        const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&h));
+        return make_double2(f.x * scale, f.y * scale);
+    }
 }
 
-// B may be F64, F32 or F16 (PB; converted to FP64 on load); A is FP64.
-// A workgroup takes one chunk of sites with one wavefront per 16-row tile of
-// G, so the B fields of the chunk are loaded by all its wavefronts at about the
-// same time and leave HBM once.
-template <int PB>
+constexpr int kGramLoads = 4;   // 16-byte words of A, and of B, per lane and stage
+
+template <int PB, int K, int NTJ>
 __global__ void __launch_bounds__(256) k_gram(const char* __restrict__ A, int na, const char* __restrict__ B, int nb,
-                                              int64_t vb, int64_t vbB, int32_t V, int32_t sites_per_wave, int nchunks,
+                                              int64_t vb, int64_t vbB, int32_t V, int32_t sites_per_chunk, int kp,
                                               double* __restrict__ partials) {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x;   // the chunk
-    if (wave >= nchunks) return;
-    const int ti = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform row tile
+    constexpr int G = PB == P64 ? 1 : PB == P32 ? 2 : 4;
+    constexpr int S = K / G;
+    constexpr int kRow = K + 1;   // odd row stride: the 16 rows of a tile fall on different banks
+    extern __shared__ double2 gram_lds[];   // [na + nb][kRow]
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
     const int t = lane & 15, kk = lane >> 4;
-    const int ntj = (nb + 15) / 16;
-    const int NI = 16 * ((na + 15) / 16), NJ = 16 * ntj;
-    const int32_t s0 = (int32_t)((int64_t)wave * sites_per_wave);
-    const int32_t s1 = (int32_t)min((int64_t)V, (int64_t)s0 + sites_per_wave);
-    const int ia = ti * 16 + t;
-    const bool va = ia < na;
-    const char* pa = A + (int64_t)(va ? ia : 0) * vb;
-    v4d re[4], im[4];
+    const int nti = (na + 15) / 16, ntj = (nb + 15) / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ti = wave % nti, part = wave / nti;
+    const int32_t s0 = (int32_t)min((int64_t)V, (int64_t)blockIdx.x * sites_per_chunk);
+    const int32_t s1 = (int32_t)min((int64_t)V, (int64_t)s0 + sites_per_chunk);
+    uint4 ra[kGramLoads], rb[kGramLoads];
+    float rs[kGramLoads];
+    // stage (component group cg, sites from s) of every row into registers
+    auto load = [&](int cg, int32_t s) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+        for (int n = 0; n < kGramLoads; ++n) {
+            const int ea = n * 256 + tid, ra_row = ea / K, e = ea % K;
+            const int32_t sa = s + e % S;
+            ra[n] = make_uint4(0, 0, 0, 0);
+            if (ra_row < na && sa < s1)
+                ra[n] = reinterpret_cast<const uint4*>(A + (int64_t)ra_row * vb)[(int64_t)(cg * G + e / S) * V + sa];
+            const int eb = n * 256 + tid, rb_row = eb / S;
+            const int32_t sb = s + eb % S;
+            rb[n] = make_uint4(0, 0, 0, 0);
+            rs[n] = 0.f;
+            if (rb_row < nb && sb < s1) {
+                const char* pb = B + (int64_t)rb_row * vbB;
+                rb[n] = reinterpret_cast<const uint4*>(pb)[(int64_t)cg * V + sb];
+                if constexpr (PB == P16) rs[n] = reinterpret_cast<const float*>(pb + (int64_t)48 * V)[sb];
+            }
+        }
+    };
+    auto stage = [&]() {
+#pragma unroll
+        for (int n = 0; n < kGramLoads; ++n) {
+            const int ea = n * 256 + tid, ra_row = ea / K, e = ea % K;
+            if (ra_row < na) gram_lds[ra_row * kRow + e] = word_comp<P64>(ra[n], 0.f, 0);
+            const int eb = n * 256 + tid, rb_row = eb / S;
+            if (rb_row < nb) {
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    gram_lds[(na + rb_row) * kRow + g * S + eb % S] = word_comp<PB>(rb[n], rs[n], g);
+            }
+        }
+    };
+    v4d re[NTJ], im[NTJ];
+#pragma unroll
+    for (int q = 0; q < NTJ; ++q) {
         re[q] = v4d{0.0, 0.0, 0.0, 0.0};
         im[q] = v4d{0.0, 0.0, 0.0, 0.0};
     }
-    for (int c = 0; c < 12; ++c) {
-        const int64_t plane = (int64_t)c * V;
-        // several steps' loads in flight at once (each step only adds into
-        // the accumulators)
-#pragma unroll 4
-        for (int32_t s = s0; s < s1; s += 4) {
-            const int32_t site = s + kk;
-            const bool vs = site < s1;
-            double2 a = make_double2(0.0, 0.0);
-            if (va && vs) a = reinterpret_cast<const double2*>(pa)[plane + site];
+    const double2* la = gram_lds + min(ti * 16 + t, na - 1) * kRow + kk;
+    const double2* lb[NTJ];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (q < ntj) {
-                    const int jb = q * 16 + t;
-                    double2 b = make_double2(0.0, 0.0);
-                    if (jb < nb && vs) b = field_comp<PB>(B + (int64_t)jb * vbB, V, c, site);
-                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[q], 0, 0, 0);
-                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[q], 0, 0, 0);
-                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[q], 0, 0, 0);
-                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[q], 0, 0, 0);
+    for (int q = 0; q < NTJ; ++q) lb[q] = gram_lds + (na + min(q * 16 + t, nb - 1)) * kRow + kk;
+    int cg = 0;
+    int32_t s = s0;
+    if (s0 < s1) load(0, s0);
+    while (s0 < s1 && cg < 12 / G) {
+        __syncthreads();   // the previous stage has been read
+        stage();
+        s += S;
+        if (s >= s1) {
+            s = s0;
+            ++cg;
+        }
+        if (cg < 12 / G) load(cg, s);
+        __syncthreads();
+        if (part < kp) {
+            for (int e = 4 * part; e < K; e += 4 * kp) {
+                const double2 a = la[e];
+#pragma unroll
+                for (int q = 0; q < NTJ; ++q) {
+                    if (q < ntj) {
+                        const double2 b = lb[q][e];
+                        re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[q], 0, 0, 0);
+                        im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[q], 0, 0, 0);
+                        re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[q], 0, 0, 0);
+                        im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[q], 0, 0, 0);
+                    }
                 }
             }
         }
     }
-    double2* out = reinterpret_cast<double2*>(partials) + (int64_t)wave * NI * NJ;
+    if (part >= kp) return;
+    const int NI = 16 * nti, NJ = 16 * ntj;
+    double2* out = reinterpret_cast<double2*>(partials) + ((int64_t)blockIdx.x * kp + part) * NI * NJ;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < NTJ; ++q) {
         if (q < ntj) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -773,12 +833,39 @@ int convert(const ndq_geom* g, const ndq_spinor* dst, const ndq_spinor* src, hip
 }
 
 namespace {
-// Site chunks of the Gram kernel: enough workgroups to fill the device, at
+// Partial tiles of the Gram kernel: enough workgroups to fill the device, at
 // least 64 sites each, and at most 32 MiB of partial tiles.
 int gram_chunks(const ndq_geom* g, int na, int nb) {
     const int64_t tile = (int64_t)16 * ((na + 15) / 16) * 16 * ((nb + 15) / 16) * 2 * sizeof(double);
     const int64_t cap = std::max<int64_t>(1, (int64_t(32) << 20) / tile);
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(4096, cap), (g->volume + 63) / 64));
+}
+
+// A stage holds K elements of every row; a lane stages at most kGramLoads words
+// of A and of B, so K = 16 serves any block, and smaller blocks take longer
+// runs (16 S bytes of each field) with the fewer accumulators they need.
+template <int PB, int K, int NTJ>
+hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
+                         double* partials, hipStream_t st) {
+    const int nti = (na + 15) / 16;
+    int kp = nti == 1 ? 4 : nti == 2 ? 2 : 1;
+    while (kp > nw) kp >>= 1;
+    const int chunks = nw / kp;
+    int32_t spc = (V + chunks - 1) / chunks;
+    spc = (spc + 63) & ~63;   // whole stages, and runs that start on a cache line
+    const size_t lds = (size_t)(na + nb) * (K + 1) * sizeof(double2);
+    hipLaunchKernelGGL((k_gram<PB, K, NTJ>), dim3(chunks), dim3(256), lds, st, A, na, B, nb, vb, vbB, V, spc, kp,
+                       partials);
+    return hipGetLastError();
+}
+
+template <int PB>
+hipError_t launch_gram(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
+                       double* partials, hipStream_t st) {
+    static_assert(64 * 16 <= 256 * kGramLoads, "a stage of 64 rows");
+    if (na <= 16 && nb <= 16) return launch_gram_k<PB, 64, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    if (na <= 32 && nb <= 32) return launch_gram_k<PB, 32, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    return launch_gram_k<PB, 16, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
 }
 }  // namespace
 
@@ -787,21 +874,34 @@ size_t gram_partials_bytes(const ndq_geom* g, int na, int nb) {
     return (size_t)gram_chunks(g, na, nb) * NI * NJ * 2 * sizeof(double);
 }
 
-int gram(const ndq_geom* g, const void* A, int na, const void* B, int nb, double* partials, double* G,
-         hipStream_t st) {
+int gram_block(const ndq_geom* g, const void* A, int na, const ndq_spinor* B, double* partials, double* G,
+               hipStream_t st) {
+    const int nb = B->nrhs;
     if (na < 1 || nb < 1 || na > 64 || nb > 64) return fail(NDQ_EINVAL, "gram: block sizes must be in [1, 64]");
     const int nw = gram_chunks(g, na, nb);
-    const int64_t V = g->volume;
-    int32_t spw = (int32_t)((V + nw - 1) / nw);
-    spw = (spw + 3) & ~3;
+    const int32_t V = (int32_t)g->volume;
     const int64_t vb = spinor_rhs_bytes(g, NDQ_F64, NDQ_FULL);
-    const dim3 block(64 * ((na + 15) / 16));
-    hipLaunchKernelGGL(k_gram<P64>, dim3(nw), block, 0, st, static_cast<const char*>(A), na, static_cast<const char*>(B),
-                       nb, vb, vb, (int32_t)V, spw, nw, partials);
-    NDQ_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, nw, G);
+    const int64_t vbB = spinor_rhs_bytes(g, B->prec, NDQ_FULL);
+    const char* a = static_cast<const char*>(A);
+    const char* b = static_cast<const char*>(B->data);
+    switch (B->prec) {
+        case NDQ_F64: NDQ_HIP(launch_gram<P64>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
+        case NDQ_F32: NDQ_HIP(launch_gram<P32>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
+        default: NDQ_HIP(launch_gram<P16>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
+    }
+    // partial tiles written: the kernel's chunks times the wavefronts sharing a row tile
+    const int nti = (na + 15) / 16;
+    int kp = nti == 1 ? 4 : nti == 2 ? 2 : 1;
+    while (kp > nw) kp >>= 1;
+    hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, nw / kp * kp, G);
     NDQ_HIP(hipGetLastError());
     return NDQ_OK;
+}
+
+int gram(const ndq_geom* g, const void* A, int na, const void* B, int nb, double* partials, double* G,
+         hipStream_t st) {
+    const ndq_spinor b = {const_cast<void*>(B), NDQ_F64, NDQ_FULL, nb};
+    return gram_block(g, A, na, &b, partials, G, st);
 }
 
 int mode_dots(const ndq_geom* g, const void* modes, int nev, const ndq_spinor* v, double* partials, double* dots,
@@ -844,30 +944,6 @@ int mode_update(const ndq_geom* g, const void* modes, int nev, const double* coe
 int mode_coef(const double* c, const double* d, const ModeSigns& sg, int use_sign, int nev, double sc, double sd,
               double* coef, hipStream_t st) {
     hipLaunchKernelGGL(k_mode_coef, dim3(1), dim3(NDQ_MAX_MODES), 0, st, c, d, sg, use_sign, nev, sc, sd, coef);
-    NDQ_HIP(hipGetLastError());
-    return NDQ_OK;
-}
-
-int gram_block(const ndq_geom* g, const void* A, int na, const ndq_spinor* B, double* partials, double* G,
-               hipStream_t st) {
-    const int nb = B->nrhs;
-    if (na < 1 || nb < 1 || na > 64 || nb > 64) return fail(NDQ_EINVAL, "gram: block sizes must be in [1, 64]");
-    const int nw = gram_chunks(g, na, nb);
-    const int64_t V = g->volume;
-    int32_t spw = (int32_t)((V + nw - 1) / nw);
-    spw = (spw + 3) & ~3;
-    const int64_t vb = spinor_rhs_bytes(g, NDQ_F64, NDQ_FULL);
-    const int64_t vbB = spinor_rhs_bytes(g, B->prec, NDQ_FULL);
-    const dim3 grid(nw), blk(64 * ((na + 15) / 16));
-    const char* a = static_cast<const char*>(A);
-    const char* b = static_cast<const char*>(B->data);
-    switch (B->prec) {
-        case NDQ_F64: hipLaunchKernelGGL(k_gram<P64>, grid, blk, 0, st, a, na, b, nb, vb, vbB, (int32_t)V, spw, nw, partials); break;
-        case NDQ_F32: hipLaunchKernelGGL(k_gram<P32>, grid, blk, 0, st, a, na, b, nb, vb, vbB, (int32_t)V, spw, nw, partials); break;
-        default: hipLaunchKernelGGL(k_gram<P16>, grid, blk, 0, st, a, na, b, nb, vb, vbB, (int32_t)V, spw, nw, partials); break;
-    }
-    NDQ_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, nw, G);
     NDQ_HIP(hipGetLastError());
     return NDQ_OK;
 }
