@@ -232,12 +232,24 @@ void clear_launch_tuning(int sprec, int lprec, int recon) {
 // fields per workgroup, and the tiles in chunks spanning two x1 rows of the
 // slice (the smallest divisor c of the slice's tiles with 64 c >= 2 s1), so
 // that the neighbour spinors of nearby tiles are still in L2 when re-read.
+// Where 8 divides the number of fields and 6 does not, 8 fields per workgroup:
+// no group is left with 2 fields or 4 (8 FP64 fields on 24^3x48 1048 -> 800 us,
+// 16 1690 -> 1554 us; 24 fields, which 6 divides, 2257 us against 2371).
 // F16 fields (half the bytes per field) keep one group in tile order.
+//
+// The full Q on F32 fields marches along x0 (k_wilson_march) from 4 fields on
+// where its 64-site columns hold 4096 slices in all, 8 for each of the 512
+// workgroups it keeps resident: measured against the tile form at 12, 8 and 4
+// fields, 24^3x48 (31104, 20736, 10368 column slices) 0.83, 0.62, 0.87 of its
+// time, 16^3x32 (6144, 4096, 2048) 0.77, 0.60, 0.92, 12^3x24 (2016, 1344, 672)
+// 0.96, 0.77, 1.14.  3 fields leave a wavefront in four without one and gain
+// from 8192 on (10368: 0.89; 4320: 1.05), 5 fields (groups of 3 and 2) never
+// do (0.93 to 1.17).
 MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, int nrhs, int ny) {
-    (void)lprec; (void)recon; (void)ny;
+    (void)lprec; (void)recon;
     MrhsShape s;
     if (nrhs >= 8 && sprec != P16) {
-        s.rg = 6;
+        s.rg = nrhs % 8 == 0 && nrhs % 6 != 0 ? 8 : 6;
         s.group_major = 1;
         const int64_t per_slice = g.vh / g.n0;
         if (g.n0 >= 4 && per_slice * g.n0 == g.vh && per_slice % 64 == 0) {
@@ -249,6 +261,10 @@ MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, in
                 }
             }
         }
+    }
+    if (sprec == P32 && ny == 2 && nrhs >= 3 && nrhs != 5) {
+        const int64_t slices = 2 * (int64_t)((g.s0 + 63) / 64) * ((nrhs + 3) / 4) * g.n0;
+        if (slices >= (nrhs == 3 ? 8192 : 4096)) s.group_major = 3;
     }
     return s;
 }
@@ -279,7 +295,7 @@ extern "C" int ndq_set_mrhs_launch(const ndq_geom* g, int sprec, int lprec, int 
     }
     ndq::MrhsShape s;
     s.rg = rg;
-    s.group_major = group_major == 2 ? 2 : group_major ? 1 : 0;
+    s.group_major = group_major == 2 || group_major == 3 ? group_major : group_major ? 1 : 0;
     s.chunk = chunk;
     s.xcd_remap = xcd_remap ? 1 : 0;
     s.link_nt = link_nt < 0 ? -1 : (link_nt ? 1 : 0);

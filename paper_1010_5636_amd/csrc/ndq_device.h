@@ -120,9 +120,86 @@ struct SpinorView {
 
 template <int P> struct SpinorIO;
 
+// A wave-uniform pointer kept in scalar registers: base[off] with a 32-bit lane
+// offset is then one load instruction, without 64-bit address arithmetic per lane.
+#define NDQ_GLOBAL __attribute__((address_space(1)))
+typedef const NDQ_GLOBAL char* gptr_t;
+__device__ __forceinline__ gptr_t scalar_ptr(const char* p) {
+    gptr_t q = (gptr_t)p;
+    asm("" : "+s"(q));
+    return q;
+}
+typedef float f32x4_v __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_v __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_v __attribute__((ext_vector_type(2)));
+
+// A neighbour spinor as the hops use it: sums of two components, the second
+// taken as is or times i, and the weight of the colour vectors derived from it.
+template <typename R>
+struct HopWeight {
+    __device__ __forceinline__ C<R> acc(C<R> a, C<R> w) const { return cadd(a, w); }
+};
+template <typename R>
+struct HopSpinor {
+    C<R> s[12];
+    __device__ __forceinline__ C<R> get(int k) const { return s[k]; }
+    __device__ __forceinline__ HopWeight<R> weight() const { return {}; }
+    __device__ __forceinline__ C<R> add(int j, int k) const { return cadd(s[j], s[k]); }
+    __device__ __forceinline__ C<R> sub(int j, int k) const { return csub(s[j], s[k]); }
+    __device__ __forceinline__ C<R> addi(int j, int k) const { return cadd(s[j], cmuli(s[k])); }
+    __device__ __forceinline__ C<R> subi(int j, int k) const { return csub(s[j], cmuli(s[k])); }
+};
+
+// F16 storage: the halves stay as stored (half2 = re, im) and the site's scale
+// enters with the accumulation, so that decoding costs no instruction of its
+// own: each sum of two halves is one mixed-precision fma (a * 1 + b) and the
+// accumulator takes scale * w by fma instead of w by add.  The multi-RHS kernel
+// kept the vector units busy all the time with every half converted and scaled
+// (1416 vector instructions per site and field): 12 fields on 24^3x48 366 us;
+// this way (1008) 348 us, bound by L2 misses like the F32 form.
+struct HopWeight16 {
+    float scale;
+    __device__ __forceinline__ C<float> acc(C<float> a, C<float> x) const {
+        return {__builtin_fmaf(scale, x.r, a.r), __builtin_fmaf(scale, x.i, a.i)};
+    }
+};
+struct HopSpinor16 {
+    uint32_t w[12];
+    float scale;
+    __device__ __forceinline__ C<float> get(int k) const { return {re(k) * scale, im(k) * scale}; }
+    __device__ __forceinline__ HopWeight16 weight() const { return {scale}; }
+    // a register 1.0f the compiler does not fold, which keeps a * 1 + b an fma of halves
+    __device__ static __forceinline__ float one() {
+        float x = 1.0f;
+        asm("" : "+s"(x));
+        return x;
+    }
+    __device__ __forceinline__ float re(int k) const { return __low2float(half(k)); }
+    __device__ __forceinline__ float im(int k) const { return __high2float(half(k)); }
+    __device__ __forceinline__ __half2 half(int k) const { return *reinterpret_cast<const __half2*>(&w[k]); }
+    __device__ __forceinline__ C<float> add(int j, int k) const {
+        const float o = one();
+        return {__builtin_fmaf(re(j), o, re(k)), __builtin_fmaf(im(j), o, im(k))};
+    }
+    __device__ __forceinline__ C<float> sub(int j, int k) const {
+        const float o = one();
+        return {__builtin_fmaf(re(j), o, -re(k)), __builtin_fmaf(im(j), o, -im(k))};
+    }
+    __device__ __forceinline__ C<float> addi(int j, int k) const {
+        const float o = one();
+        return {__builtin_fmaf(re(j), o, -im(k)), __builtin_fmaf(im(j), o, re(k))};
+    }
+    __device__ __forceinline__ C<float> subi(int j, int k) const {
+        const float o = one();
+        return {__builtin_fmaf(re(j), o, im(k)), __builtin_fmaf(im(j), o, -re(k))};
+    }
+};
+
 template <> struct SpinorIO<P64> {
     using R = double;
+    using Hop = HopSpinor<double>;
     static constexpr int kBytesPerSite = 192;
+    __device__ static __forceinline__ void load_hop(const SpinorView& v, int64_t s, Hop& h) { load(v, s, h.s); }
     __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, C<R> out[12]) {
         const double2* p = reinterpret_cast<const double2*>(v.base) + s;
 #pragma unroll
@@ -148,7 +225,24 @@ template <> struct SpinorIO<P64> {
 
 template <> struct SpinorIO<P32> {
     using R = float;
+    using Hop = HopSpinor<float>;
     static constexpr int kBytesPerSite = 96;
+    __device__ static __forceinline__ void load_hop(const SpinorView& v, int64_t s, Hop& h) { load(v, s, h.s); }
+    // planes at `base` + j * plane (wave-uniform), site at byte offset off of each
+    __device__ static __forceinline__ void load_hop_at(const char* base, int64_t plane, uint32_t off, Hop& h) {
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const f32x4_v w = *(const NDQ_GLOBAL f32x4_v*)(scalar_ptr(base + j * plane) + off);
+            h.s[2 * j] = {w.x, w.y};
+            h.s[2 * j + 1] = {w.z, w.w};
+        }
+    }
+    __device__ static __forceinline__ void store_nt(char* base, int64_t plane, uint32_t off, const C<R> in[12]) {
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+            __builtin_nontemporal_store(f32x4_v{in[2 * j].r, in[2 * j].i, in[2 * j + 1].r, in[2 * j + 1].i},
+                                        reinterpret_cast<f32x4_v*>(base + j * plane + off));
+    }
     __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, C<R> out[12]) {
         const float4* p = reinterpret_cast<const float4*>(v.base) + s;
 #pragma unroll
@@ -185,7 +279,20 @@ template <> struct SpinorIO<P32> {
 
 template <> struct SpinorIO<P16> {
     using R = float;
+    using Hop = HopSpinor16;
     static constexpr int kBytesPerSite = 52;
+    __device__ static __forceinline__ void load_hop(const SpinorView& v, int64_t s, Hop& h) {
+        const uint4* p = reinterpret_cast<const uint4*>(v.base) + s;
+        h.scale = reinterpret_cast<const float*>(v.base + (int64_t)48 * v.stride)[s];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint4 w = p[(int64_t)j * v.stride];
+            h.w[4 * j] = w.x;
+            h.w[4 * j + 1] = w.y;
+            h.w[4 * j + 2] = w.z;
+            h.w[4 * j + 3] = w.w;
+        }
+    }
     __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, C<R> out[12]) {
         const uint4* p = reinterpret_cast<const uint4*>(v.base) + s;
         const float scale = reinterpret_cast<const float*>(v.base + (int64_t)48 * v.stride)[s];
@@ -258,9 +365,6 @@ struct LinkFmt {
 // words that neighbouring sites re-read from the caches; a full Q apply reads
 // each link twice (as forward link of its site and backward link of the
 // neighbour), and there the second read should find it cached (NT = false).
-typedef unsigned int u32x4_v __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_v __attribute__((ext_vector_type(2)));
-
 template <bool NT, typename T>
 __device__ __forceinline__ T load_hinted(const T* p) {
     if constexpr (NT) return __builtin_nontemporal_load(p);

@@ -69,10 +69,10 @@ inline int recon_index(int recon) { return recon == 18 ? 0 : recon == 12 ? 1 : 2
 
 // Work order of the multi-right-hand-side stencil (see k_wilson_mrhs): rg
 // right-hand sides per workgroup (0: all), group-major or tile-major order of
-// the groups, tile-order chunk (-1: tile_order's choice, 0: index order), XCD
-// remap.  Looked up per (lattice, spinor precision, link precision, recon,
-// nrhs, output parities); set by ndq_set_mrhs_launch or the autotuner, else
-// the default below.
+// the groups (group_major 3: the march along x0 of k_wilson_march), tile-order
+// chunk (-1: tile_order's choice, 0: index order), XCD remap.  Looked up per
+// (lattice, spinor precision, link precision, recon, nrhs, output parities); set
+// by ndq_set_mrhs_launch or the autotuner, else the default below.
 struct MrhsShape {
     int rg = 0;
     int group_major = 0;

@@ -25,27 +25,28 @@ using namespace ndq;
 
 namespace {
 
-// spin s, colour c -> component index 3*s + c
-template <int MU, typename R>
-__device__ __forceinline__ void hop_fwd(const C<R> s[12], const C<R> u[3][3], C<R> acc[12]) {
+// spin s, colour c -> component index 3*s + c; S: HopSpinor<R> or HopSpinor16
+template <int MU, typename R, typename S>
+__device__ __forceinline__ void hop_fwd(const S& s, const C<R> u[3][3], C<R> acc[12]) {
     C<R> h0[3], h1[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         if constexpr (MU == 0) {
-            h0[c] = cadd(s[c], s[6 + c]);
-            h1[c] = cadd(s[3 + c], s[9 + c]);
+            h0[c] = s.add(c, 6 + c);
+            h1[c] = s.add(3 + c, 9 + c);
         } else if constexpr (MU == 1) {
-            h0[c] = cadd(s[c], cmuli(s[9 + c]));
-            h1[c] = cadd(s[3 + c], cmuli(s[6 + c]));
+            h0[c] = s.addi(c, 9 + c);
+            h1[c] = s.addi(3 + c, 6 + c);
         } else if constexpr (MU == 2) {
-            h0[c] = cadd(s[c], s[9 + c]);
-            h1[c] = csub(s[3 + c], s[6 + c]);
+            h0[c] = s.add(c, 9 + c);
+            h1[c] = s.sub(3 + c, 6 + c);
         } else {
-            h0[c] = cadd(s[c], cmuli(s[6 + c]));
-            h1[c] = csub(s[3 + c], cmuli(s[9 + c]));
+            h0[c] = s.addi(c, 6 + c);
+            h1[c] = s.subi(3 + c, 9 + c);
         }
     }
     C<R> w0[3], w1[3];
+    const auto wt = s.weight();
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         w0[r] = cmul(u[r][0], h0[0]);
@@ -57,45 +58,44 @@ __device__ __forceinline__ void hop_fwd(const C<R> s[12], const C<R> u[3][3], C<
     }
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-        acc[r] = cadd(acc[r], w0[r]);
-        acc[3 + r] = cadd(acc[3 + r], w1[r]);
+        acc[r] = wt.acc(acc[r], w0[r]);
+        acc[3 + r] = wt.acc(acc[3 + r], w1[r]);
         if constexpr (MU == 0) {
-            acc[6 + r] = cadd(acc[6 + r], w0[r]);
-            acc[9 + r] = cadd(acc[9 + r], w1[r]);
+            acc[6 + r] = wt.acc(acc[6 + r], w0[r]);
+            acc[9 + r] = wt.acc(acc[9 + r], w1[r]);
         } else if constexpr (MU == 1) {
-            acc[6 + r] = cadd(acc[6 + r], cmulmi(w1[r]));
-            acc[9 + r] = cadd(acc[9 + r], cmulmi(w0[r]));
+            acc[6 + r] = wt.acc(acc[6 + r], cmulmi(w1[r]));
+            acc[9 + r] = wt.acc(acc[9 + r], cmulmi(w0[r]));
         } else if constexpr (MU == 2) {
-            acc[6 + r] = csub(acc[6 + r], w1[r]);
-            acc[9 + r] = cadd(acc[9 + r], w0[r]);
+            acc[6 + r] = wt.acc(acc[6 + r], cneg(w1[r]));
+            acc[9 + r] = wt.acc(acc[9 + r], w0[r]);
         } else {
-            acc[6 + r] = cadd(acc[6 + r], cmulmi(w0[r]));
-            acc[9 + r] = cadd(acc[9 + r], cmuli(w1[r]));
+            acc[6 + r] = wt.acc(acc[6 + r], cmulmi(w0[r]));
+            acc[9 + r] = wt.acc(acc[9 + r], cmuli(w1[r]));
         }
     }
 }
 
-template <int MU, typename R>
-__device__ __forceinline__ void hop_bwd(const C<R> s[12], const C<R> u[3][3], C<R> acc[12]) {
+template <int MU, typename R, typename S>
+__device__ __forceinline__ void hop_bwd_mul(const S& s, const C<R> u[3][3], C<R> w0[3], C<R> w1[3]) {
     C<R> g0[3], g1[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         if constexpr (MU == 0) {
-            g0[c] = csub(s[c], s[6 + c]);
-            g1[c] = csub(s[3 + c], s[9 + c]);
+            g0[c] = s.sub(c, 6 + c);
+            g1[c] = s.sub(3 + c, 9 + c);
         } else if constexpr (MU == 1) {
-            g0[c] = csub(s[c], cmuli(s[9 + c]));
-            g1[c] = csub(s[3 + c], cmuli(s[6 + c]));
+            g0[c] = s.subi(c, 9 + c);
+            g1[c] = s.subi(3 + c, 6 + c);
         } else if constexpr (MU == 2) {
-            g0[c] = csub(s[c], s[9 + c]);
-            g1[c] = cadd(s[3 + c], s[6 + c]);
+            g0[c] = s.sub(c, 9 + c);
+            g1[c] = s.add(3 + c, 6 + c);
         } else {
-            g0[c] = csub(s[c], cmuli(s[6 + c]));
-            g1[c] = cadd(s[3 + c], cmuli(s[9 + c]));
+            g0[c] = s.subi(c, 6 + c);
+            g1[c] = s.addi(3 + c, 9 + c);
         }
     }
     // w = U^H g
-    C<R> w0[3], w1[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         w0[r] = cmulc(u[0][r], g0[0]);
@@ -105,24 +105,35 @@ __device__ __forceinline__ void hop_bwd(const C<R> s[12], const C<R> u[3][3], C<
         w0[r] = cfmac(w0[r], u[2][r], g0[2]);
         w1[r] = cfmac(w1[r], u[2][r], g1[2]);
     }
+}
+
+template <int MU, typename R, typename W>
+__device__ __forceinline__ void hop_bwd_acc(const W& s, const C<R> w0[3], const C<R> w1[3], C<R> acc[12]) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-        acc[r] = cadd(acc[r], w0[r]);
-        acc[3 + r] = cadd(acc[3 + r], w1[r]);
+        acc[r] = s.acc(acc[r], w0[r]);
+        acc[3 + r] = s.acc(acc[3 + r], w1[r]);
         if constexpr (MU == 0) {
-            acc[6 + r] = csub(acc[6 + r], w0[r]);
-            acc[9 + r] = csub(acc[9 + r], w1[r]);
+            acc[6 + r] = s.acc(acc[6 + r], cneg(w0[r]));
+            acc[9 + r] = s.acc(acc[9 + r], cneg(w1[r]));
         } else if constexpr (MU == 1) {
-            acc[6 + r] = cadd(acc[6 + r], cmuli(w1[r]));
-            acc[9 + r] = cadd(acc[9 + r], cmuli(w0[r]));
+            acc[6 + r] = s.acc(acc[6 + r], cmuli(w1[r]));
+            acc[9 + r] = s.acc(acc[9 + r], cmuli(w0[r]));
         } else if constexpr (MU == 2) {
-            acc[6 + r] = cadd(acc[6 + r], w1[r]);
-            acc[9 + r] = csub(acc[9 + r], w0[r]);
+            acc[6 + r] = s.acc(acc[6 + r], w1[r]);
+            acc[9 + r] = s.acc(acc[9 + r], cneg(w0[r]));
         } else {
-            acc[6 + r] = cadd(acc[6 + r], cmuli(w0[r]));
-            acc[9 + r] = cadd(acc[9 + r], cmulmi(w1[r]));
+            acc[6 + r] = s.acc(acc[6 + r], cmuli(w0[r]));
+            acc[9 + r] = s.acc(acc[9 + r], cmulmi(w1[r]));
         }
     }
+}
+
+template <int MU, typename R, typename S>
+__device__ __forceinline__ void hop_bwd(const S& s, const C<R> u[3][3], C<R> acc[12]) {
+    C<R> w0[3], w1[3];
+    hop_bwd_mul<MU>(s, u, w0, w1);
+    hop_bwd_acc<MU>(s.weight(), w0, w1, acc);
 }
 
 struct NoLoads {
@@ -138,15 +149,15 @@ __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, 
                                          More more = More()) {
     using R = typename SpinorIO<SP>::R;
     using F = LinkFmt<LP, RECON>;
-    C<R> sf[12], sb[12];
+    typename SpinorIO<SP>::Hop sf, sb;
     uint32_t wf[F::kWords], wb[F::kWords];
     C<typename LinkReal<LP>::R> u[3][3];
     if constexpr (SP != P64 || PAIR64) {
         // all loads of both hops first: one memory round trip instead of two
         // (FP64 otherwise keeps the two trips: its registers would cut the occupancy)
-        SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[MU], sf);
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[MU], sf);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, p * 4 + MU, i, wf);
-        SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, (1 - p) * 4 + MU, nb[4 + MU], wb);
         more();
         __builtin_amdgcn_sched_barrier(0);   // keep the arithmetic below every load
@@ -155,16 +166,46 @@ __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, 
         link_decode<LP, RECON>(wb, u);
         hop_bwd<MU>(sb, u, acc);
     } else {
-        SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[MU], sf);
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[MU], sf);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, p * 4 + MU, i, wf);
         link_decode<LP, RECON>(wf, u);
         hop_fwd<MU>(sf, u, acc);
-        SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[4 + MU], sb);
         link_load_words<LP, RECON, NT>(a.links, a.g.vh, (1 - p) * 4 + MU, nb[4 + MU], wb);
         more();
         link_decode<LP, RECON>(wb, u);
         hop_bwd<MU>(sb, u, acc);
     }
+}
+
+// The one-lane kernels (k_wilson, the multi-RHS tile and the march along x0) add
+// the hops of a site in one order: -0, +1, -1, +2, -2, +3, -3, +0.  The last is
+// the one a march along x0 has last, so that all of them round alike.
+// Two consecutive hops of that order: backward MUB, then forward MUF; the loads
+// of both first, except for FP64, whose registers would cut the occupancy.
+template <int SP, int LP, int RECON, int MUB, bool NT>
+__device__ __forceinline__ void hop_chain(const WilsonArgs& a, int p, int32_t i, const int32_t nb[8],
+                                          const SpinorView& vin, C<typename SpinorIO<SP>::R> acc[12]) {
+    constexpr int MUF = (MUB + 1) & 3;
+    using F = LinkFmt<LP, RECON>;
+    typename SpinorIO<SP>::Hop sf, sb;
+    uint32_t wf[F::kWords], wb[F::kWords];
+    C<typename LinkReal<LP>::R> u[3][3];
+    SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[4 + MUB], sb);
+    link_load_words<LP, RECON, NT>(a.links, a.g.vh, (1 - p) * 4 + MUB, nb[4 + MUB], wb);
+    if constexpr (SP != P64) {
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[MUF], sf);
+        link_load_words<LP, RECON, NT>(a.links, a.g.vh, p * 4 + MUF, i, wf);
+        __builtin_amdgcn_sched_barrier(0);   // keep the arithmetic below every load
+    }
+    link_decode<LP, RECON>(wb, u);
+    hop_bwd<MUB>(sb, u, acc);
+    if constexpr (SP == P64) {
+        SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[MUF], sf);
+        link_load_words<LP, RECON, NT>(a.links, a.g.vh, p * 4 + MUF, i, wf);
+    }
+    link_decode<LP, RECON>(wf, u);
+    hop_fwd<MUF>(sf, u, acc);
 }
 
 __device__ __forceinline__ double coef(const Coef& c) { return c.d ? c.f * (*c.d) : c.f; }
@@ -231,10 +272,10 @@ __global__ void __launch_bounds__(BLOCK) k_wilson(WilsonArgs a) {
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
         const SpinorView& vin = a.in[y];
-        hop_pair<SP, LP, RECON, 0, NT>(a, p, i, nb, vin, acc);
-        hop_pair<SP, LP, RECON, 1, NT>(a, p, i, nb, vin, acc);
-        hop_pair<SP, LP, RECON, 2, NT>(a, p, i, nb, vin, acc);
-        hop_pair<SP, LP, RECON, 3, NT>(a, p, i, nb, vin, acc);
+        hop_chain<SP, LP, RECON, 0, NT>(a, p, i, nb, vin, acc);
+        hop_chain<SP, LP, RECON, 1, NT>(a, p, i, nb, vin, acc);
+        hop_chain<SP, LP, RECON, 2, NT>(a, p, i, nb, vin, acc);
+        hop_chain<SP, LP, RECON, 3, NT>(a, p, i, nb, vin, acc);
 
         const R b = (R)a.b_hop;
         if (a.has_self) {
@@ -509,29 +550,29 @@ __device__ __forceinline__ void mrhs_tile(const GeomK& g, const char* links, int
         C<R> acc[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
-        // spinor loads of both hops of a direction first (one memory round
-        // trip per direction; FP64: one per hop, for its registers); the
-        // arithmetic order stays fwd 0, bwd 0, fwd 1, ...
+        // the order of hop_chain, the spinor loads of two hops first (one memory
+        // round trip per pair; FP64: one per hop, for its registers)
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
-            C<R> sf[12], sb[12];
+            const int mf = (mu + 1) & 3;
+            typename SpinorIO<SP>::Hop sf, sb;
             C<LR> u[3][3];
-            SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[mu], sf);
+            SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[4 + mu], sb);
             if constexpr (SP != P64) {
-                SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + mu], sb);
+                SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[mf], sf);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            SL::get(lw, mu, lo, u);
-            if (mu == 0) hop_fwd<0>(sf, u, acc);
-            if (mu == 1) hop_fwd<1>(sf, u, acc);
-            if (mu == 2) hop_fwd<2>(sf, u, acc);
-            if (mu == 3) hop_fwd<3>(sf, u, acc);
-            if constexpr (SP == P64) SpinorIO<SP>::load(vin, (int64_t)vin.site0 + nb[4 + mu], sb);
             SL::get(lw, 4 + mu, lo, u);
             if (mu == 0) hop_bwd<0>(sb, u, acc);
             if (mu == 1) hop_bwd<1>(sb, u, acc);
             if (mu == 2) hop_bwd<2>(sb, u, acc);
             if (mu == 3) hop_bwd<3>(sb, u, acc);
+            if constexpr (SP == P64) SpinorIO<SP>::load_hop(vin, (int64_t)vin.site0 + nb[mf], sf);
+            SL::get(lw, mf, lo, u);
+            if (mf == 0) hop_fwd<0>(sf, u, acc);
+            if (mf == 1) hop_fwd<1>(sf, u, acc);
+            if (mf == 2) hop_fwd<2>(sf, u, acc);
+            if (mf == 3) hop_fwd<3>(sf, u, acc);
         }
         const R b = (R)b_hop;
         if (self) {
@@ -657,6 +698,275 @@ hipError_t launch_mrhs_fmt(const WilsonArgs& a, const MrhsGrid& m, int link_nt, 
     return nt ? launch_mrhs_nt<SP, LP, RECON, true>(a, m, st) : launch_mrhs_nt<SP, LP, RECON, false>(a, m, st);
 }
 
+// Many F32 right-hand sides on one gauge field, full Q, as a march along x0.
+//
+// The multi-RHS stencil is bound by what misses the L2s (about 6 TB/s on this
+// card, from the last-level cache as from HBM).  In the tile form above a
+// spinor misses 3 to 4 times: its x0 neighbours lie a whole slice of tiles
+// away, and 4 MB of L2 per XCD do not hold what 128 workgroups of several
+// fields read between the uses.  Here a workgroup of 4 wavefronts (one field
+// each) owns a column of 64 sites of one parity per slice and walks T slices:
+//   * psi(t - 1) and psi(t) of the column stay in registers, so a site takes 7
+//     spinor loads instead of 9, and its x0 link one load instead of two;
+//   * out(t - 1) gets its last hop (+0, which reads psi(t)) in step t, so that
+//     every load of slice t, from the column itself and from the columns next to
+//     it, falls into the same step and all but the first find it in L2.
+// The 7 links of a step (fields share them) go to LDS, two buffers in turn, one
+// barrier per step.  The hops, their order and the epilogue are those of
+// k_wilson, so the results equal it bit for bit.  Outputs are stored with the
+// non-temporal hint: nothing in the launch reads them.  About 235 registers, two
+// wavefronts per SIMD.
+// Measured, tile form -> march: 12 fields on 24^3x48, 12-real links, 640 -> 521 us;
+// on 32^3x64, 18-real links, 2110 -> 1868 us (L2 misses 12.9 -> 10.8 GB).  Tried
+// and not kept: the next slice's x1 neighbours in flight across the barrier
+// (spills); FP64 (its registers); F16 fields (375 us against 348 us: half the
+// traffic, and the tile form's three wavefronts per SIMD hide more).
+template <int N, typename R>
+__device__ __forceinline__ void pin(C<R> (&x)[N]) {   // computed here, not sunk below the stores
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(x[k].r), "+v"(x[k].i));
+}
+
+struct MarchArgs {
+    GeomK g;
+    const char* links;
+    const char* in;            // full fields, right-hand side 0
+    char* out;
+    const char* v[3];
+    int64_t rhs_bytes;         // of every field
+    int64_t plane;             // bytes between planes
+    double a_self;
+    Coef c0;
+    Coef cv[3];
+    int nrhs, ngroups;
+    int32_t tiles;             // tiles of 64 sites per parity and x0 slice
+    int32_t T, nseg;           // slices per segment, segments
+};
+
+template <int LP, int RECON, int NV>
+__global__ void __launch_bounds__(256, 2) k_wilson_march(MarchArgs a) {
+    using R = float;
+    using IO = SpinorIO<P32>;
+    using Hop = typename IO::Hop;
+    using LR = typename LinkReal<LP>::R;
+    using F = LinkFmt<LP, RECON>;
+    using SL = StagedLinks<LP, RECON>;
+    constexpr int kBuf = 7 * SL::kWords * 64;
+    extern __shared__ uint32_t lw[];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned lin = xcd_remap(blockIdx.x, gridDim.x);
+    const int par = (int)(lin & 1u);
+    lin >>= 1;
+    const int32_t tile = (int32_t)(lin % (unsigned)a.tiles);
+    lin /= (unsigned)a.tiles;
+    const int seg = (int)(lin % (unsigned)a.nseg);
+    const int grp = (int)(lin / (unsigned)a.nseg);
+    // the fields split evenly over the groups, at most 4 each; a wavefront
+    // without one still stages links
+    const int r0 = grp * a.nrhs / a.ngroups, r1 = (grp + 1) * a.nrhs / a.ngroups;
+    const int r = r0 + w;
+    const bool field = r < r1;
+    const GeomK& g = a.g;
+    const int32_t jt = tile * 64 + lane;
+    const bool active = jt < g.s0;
+    const int32_t j = min(jt, g.s0 - 1);
+    // offsets of the in-slice neighbours: constant along x0
+    int32_t d[8];
+    {
+        const uint32_t q = fdiv((uint32_t)j, g.d_nh3);
+        const int32_t x3h = j - (int32_t)q * g.nh3;
+        const uint32_t x1 = fdiv(q, g.d_n2);
+        const int32_t x2 = (int32_t)q - (int32_t)x1 * g.n2;
+        const int bit = (par + (int)x1 + x2) & 1;
+        d[1] = ((int32_t)x1 == g.n1 - 1) ? -(g.n1 - 1) * g.s1 : g.s1;
+        d[5] = (x1 == 0) ? (g.n1 - 1) * g.s1 : -g.s1;
+        d[2] = (x2 == g.n2 - 1) ? -(g.n2 - 1) * g.nh3 : g.nh3;
+        d[6] = (x2 == 0) ? (g.n2 - 1) * g.nh3 : -g.nh3;
+        d[3] = bit == 0 ? 0 : (x3h == g.nh3 - 1) ? 1 - g.nh3 : 1;
+        d[7] = bit == 1 ? 0 : (x3h == 0) ? g.nh3 - 1 : -1;
+    }
+    const int32_t dbw = w == 1 ? d[5] : w == 2 ? d[6] : d[7];
+    const R as = (R)a.a_self, b = R(-0.5), c0 = (R)coef(a.c0);
+    R cv[NV > 0 ? NV : 1];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) cv[k] = (R)coef(a.cv[k]);
+    const int t0 = seg * a.T;
+    const int t1 = min(g.n0, t0 + a.T);
+    int p = (par + t0) & 1;
+    const char* in = a.in + (int64_t)(field ? r : r0) * a.rhs_bytes;
+    uint32_t wf[F::kWords], wb[F::kWords];
+    // links of step t (sites of parity pp in slice t): wavefront 0 the x0 links of
+    // slice t - 1, wavefront k the links k of the sites and of their neighbours x - k
+    auto link_loads = [&](int pp, int t) {
+        const int32_t tt = min(t, t1 - 1);
+        const int32_t i = tt * g.s0 + j;
+        const int32_t im = (t == 0 ? g.n0 - 1 : t - 1) * g.s0 + j;
+        link_load_words<LP, RECON>(a.links, g.vh, w == 0 ? (1 - pp) * 4 : pp * 4 + w, w == 0 ? im : i, wf);
+        if (w > 0) link_load_words<LP, RECON>(a.links, g.vh, (1 - pp) * 4 + w, i + dbw, wb);
+    };
+    auto link_stage = [&](uint32_t* buf) {
+        SL::put(buf, w, lane, wf);
+        if (w > 0) SL::put(buf, 3 + w, lane, wb);
+    };
+    auto own = [&](int pp, int t) { return 16u * (uint32_t)(pp * g.vh + t * g.s0 + j); };
+    link_loads(p, t0);
+    Hop cur, prev;
+    C<R> q[12];   // out(t - 1) but for its last hop, then out(t)
+    IO::load_hop_at(in, a.plane, own(1 - p, t0 == 0 ? g.n0 - 1 : t0 - 1), prev);
+    IO::load_hop_at(in, a.plane, own(p, t0), cur);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) q[k] = {R(0), R(0)};
+    link_stage(lw);
+    int cb = 0;
+#pragma unroll 1
+    for (int t = t0; t <= t1; ++t) {
+        __syncthreads();
+        const uint32_t* buf = lw + cb * kBuf;
+        const uint32_t ob = own(1 - p, t);
+        Hop s1, s2, s3, s4, nx;
+        C<LR> u[3][3];
+        C<R> acc[12];
+        if (t < t1) link_loads(1 - p, t + 1);
+        if (field) {
+            Hop vv[NV > 0 ? NV : 1];
+            if (NV > 0) {
+                // slice t0 has nothing to finish yet: it loads its own sites' words
+                const uint32_t om = t > t0 ? own(1 - p, t - 1) : own(p, t);
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+                    IO::load_hop_at(a.v[k] + (int64_t)r * a.rhs_bytes, a.plane, om, vv[k]);
+            }
+            if (NV == 0 && t < t1) {
+                IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[1], s1);
+                IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[5], s2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            SL::get(buf, 0, lane, u);
+            hop_fwd<0>(cur, u, q);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
+            hop_bwd<0>(prev, u, acc);
+            pin(acc);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const C<R> x = prev.get(k);
+                q[k] = {as * x.r + b * q[k].r, as * x.i + b * q[k].i};
+                if (k >= 6) q[k] = cneg(q[k]);
+                q[k] = cscale(c0, q[k]);
+            }
+            pin(q);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NV > 0) {
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) {
+                        const C<R> x = vv[k].get(c);
+                        q[c] = {q[c].r + cv[k] * x.r, q[c].i + cv[k] * x.i};
+                    }
+                pin(q);
+            }
+            if (active && t > t0) IO::store_nt(a.out + (int64_t)r * a.rhs_bytes, a.plane, own(1 - p, t - 1), q);
+        }
+        if (t == t1) break;
+        if (field) {
+            if (NV > 0) {
+                IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[1], s1);
+                IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[5], s2);
+            }
+            IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[2], s3);
+            IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[6], s4);
+            __builtin_amdgcn_sched_barrier(0);
+            SL::get(buf, 1, lane, u);
+            hop_fwd<1>(s1, u, acc);
+            SL::get(buf, 4, lane, u);
+            hop_bwd<1>(s2, u, acc);
+            pin(acc);
+            IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[3], s1);
+            IO::load_hop_at(in, a.plane, ob + 16u * (uint32_t)d[7], s2);
+            __builtin_amdgcn_sched_barrier(0);
+            SL::get(buf, 2, lane, u);
+            hop_fwd<2>(s3, u, acc);
+            SL::get(buf, 5, lane, u);
+            hop_bwd<2>(s4, u, acc);
+            pin(acc);
+            IO::load_hop_at(in, a.plane, own(1 - p, t + 1 == g.n0 ? 0 : t + 1), nx);
+            __builtin_amdgcn_sched_barrier(0);
+            SL::get(buf, 3, lane, u);
+            hop_fwd<3>(s1, u, acc);
+            SL::get(buf, 6, lane, u);
+            hop_bwd<3>(s2, u, acc);
+            pin(acc);
+            prev = cur;
+            cur = nx;
+#pragma unroll
+            for (int k = 0; k < 12; ++k) q[k] = acc[k];
+        }
+        cb ^= 1;   // the other buffer was last read before this step's barrier
+        link_stage(lw + cb * kBuf);
+        p = 1 - p;
+    }
+}
+
+// Slices per workgroup: the T that takes the fewest steps in all, rounds of
+// `resident` workgroups times T slices and the two extra loads at a segment's
+// ends (24^3x48, 12 fields, resident 512: T = 16, 521 us; 12: 541, 24: 566).
+int march_slices(const GeomK& g, int nrhs, int resident) {
+    const int64_t columns = 2 * (int64_t)((g.s0 + 63) / 64) * ((nrhs + 3) / 4);
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int T = 1; T <= g.n0; ++T) {
+        const int64_t wgs = columns * ((g.n0 + T - 1) / T);
+        const int64_t c = (wgs + resident - 1) / resident * (2 * T + 3);
+        if (c < cost) {
+            cost = c;
+            best = T;
+        }
+    }
+    return best;
+}
+
+template <int LP, int RECON>
+hipError_t launch_march(const WilsonArgs& a, int nrhs, hipStream_t st) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    MarchArgs m;
+    memset(&m, 0, sizeof(m));
+    m.g = a.g;
+    m.links = a.links;
+    m.in = a.in[0].base;
+    m.out = a.out[0].base;
+    m.rhs_bytes = a.in[0].rhs_bytes;
+    m.plane = (int64_t)a.in[0].stride * 16;
+    for (int k = 0; k < a.nv; ++k) {
+        m.v[k] = a.v[k][0].base;
+        m.cv[k] = a.cv[k];
+    }
+    m.a_self = a.a_self;
+    m.c0 = a.c0;
+    m.nrhs = nrhs;
+    m.ngroups = (nrhs + 3) / 4;
+    m.tiles = (a.g.s0 + 63) / 64;
+    m.T = march_slices(a.g, nrhs, 2 * cus);
+    m.nseg = (a.g.n0 + m.T - 1) / m.T;
+    const dim3 grid(2u * (unsigned)m.tiles * (unsigned)m.nseg * (unsigned)m.ngroups);
+    const size_t lds = (size_t)2 * 7 * StagedLinks<LP, RECON>::kWords * 64 * sizeof(uint32_t);
+    auto go = [&](auto kernel) -> hipError_t {
+        const hipError_t er = allow_lds(kernel, lds);
+        if (er != hipSuccess) return er;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, st, m);
+        return hipGetLastError();
+    };
+    switch (a.nv) {
+        case 0: return go(&k_wilson_march<LP, RECON, 0>);
+        case 2: return go(&k_wilson_march<LP, RECON, 2>);
+        default: return go(&k_wilson_march<LP, RECON, 3>);
+    }
+}
+
 // Q on several lattices (each with its own links and right-hand sides) in one
 // persistent launch: the tiles of all lattices (both output parities) form one
 // list; a grid of a fixed number of workgroups (a small multiple of what the
@@ -780,6 +1090,29 @@ hipError_t launch_wilson(int sprec, int lprec, int recon, const WilsonArgs& args
     }
 }
 
+namespace {
+// Launches the march can take: full F32 fields, Q with the same field as stencil
+// input and same-site term, 0, 2 or 3 extra vectors, 32-bit byte offsets.
+bool march_fits(const WilsonArgs& a, int sprec, int ny, int nrhs) {
+    if (sprec != P32 || ny != 2 || a.p0 != 0 || !a.has_self || !a.gamma5 || a.b_hop != -0.5 || a.partials ||
+        a.nv == 1 || nrhs < 3 || (int64_t)a.g.vh * 32 >= INT32_MAX)
+        return false;
+    const int32_t stride = 2 * a.g.vh;
+    for (int p = 0; p < 2; ++p) {
+        const SpinorView *in = &a.in[p], *self = &a.self[p], *out = &a.out[p];
+        if (in->base != a.in[0].base || self->base != a.in[0].base || out->base != a.out[0].base ||
+            in->site0 != (1 - p) * a.g.vh || self->site0 != p * a.g.vh || out->site0 != p * a.g.vh ||
+            in->stride != stride || out->stride != stride || out->rhs_bytes != a.in[0].rhs_bytes)
+            return false;
+        for (int k = 0; k < a.nv; ++k)
+            if (a.v[k][p].base != a.v[k][0].base || a.v[k][p].site0 != p * a.g.vh || a.v[k][p].stride != stride ||
+                a.v[k][p].rhs_bytes != a.in[0].rhs_bytes)
+                return false;
+    }
+    return true;
+}
+}  // namespace
+
 hipError_t launch_wilson_mrhs(int sprec, int lprec, int recon, const WilsonArgs& args, int ny, int nrhs,
                               hipStream_t st) {
     WilsonArgs a = args;
@@ -791,7 +1124,7 @@ hipError_t launch_wilson_mrhs(int sprec, int lprec, int recon, const WilsonArgs&
     m.ny = ny;
     m.rg = std::max(1, std::min(sh.rg > 0 ? sh.rg : nrhs, nrhs));
     m.ngroups = (nrhs + m.rg - 1) / m.rg;
-    m.group_major = sh.group_major;
+    m.group_major = sh.group_major == 3 ? 1 : sh.group_major;   // 3 and no march: the tiles group-major
     m.nrhs = nrhs;
     m.per_part = 0;
     if (m.group_major == 2) {
@@ -803,6 +1136,16 @@ hipError_t launch_wilson_mrhs(int sprec, int lprec, int recon, const WilsonArgs&
         }
     }
     const int key = sprec * 1000 + lprec * 100 + recon;
+    if (sh.group_major == 3 && march_fits(a, sprec, ny, nrhs)) {
+        switch (lprec * 100 + recon) {
+            case P32 * 100 + 18: return launch_march<P32, 18>(a, nrhs, st);
+            case P32 * 100 + 12: return launch_march<P32, 12>(a, nrhs, st);
+            case P32 * 100 + 8: return launch_march<P32, 8>(a, nrhs, st);
+            case P16 * 100 + 18: return launch_march<P16, 18>(a, nrhs, st);
+            case P16 * 100 + 12: return launch_march<P16, 12>(a, nrhs, st);
+            default: return hipErrorInvalidValue;
+        }
+    }
     switch (key) {
         case P64 * 1000 + P64 * 100 + 18: return launch_mrhs_fmt<P64, P64, 18>(a, m, sh.link_nt, st);
         case P64 * 1000 + P64 * 100 + 12: return launch_mrhs_fmt<P64, P64, 12>(a, m, sh.link_nt, st);
