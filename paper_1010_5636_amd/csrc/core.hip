@@ -9,16 +9,6 @@
 namespace {
 thread_local char g_last_error[512] = "";
 
-ndq::FastDiv make_fastdiv(uint32_t d) {
-    uint32_t l = 0;
-    while ((1ull << l) < d) ++l;
-    const uint64_t num = 1ull << (31 + l);
-    ndq::FastDiv f;
-    f.m = (uint32_t)((num + d - 1) / d);
-    f.s = 31 + l;
-    return f;
-}
-
 // The multiply-shift identity holds for every n < 2^31; check it on the
 // values the kernels can produce (all n below the lattice volume).
 bool fastdiv_ok(ndq::FastDiv f, uint32_t d, uint32_t nmax) {
@@ -138,9 +128,9 @@ int ndq_geom_create(const int32_t dims[4], ndq_geom** out) {
     k.s1 = dims[2] * k.nh3;
     k.s0 = dims[1] * k.s1;
     k.vh = g->vh;
-    k.d_nh3 = make_fastdiv((uint32_t)k.nh3);
-    k.d_n2 = make_fastdiv((uint32_t)k.n2);
-    k.d_n1 = make_fastdiv((uint32_t)k.n1);
+    k.d_nh3 = ndq::make_fastdiv((uint32_t)k.nh3);
+    k.d_n2 = ndq::make_fastdiv((uint32_t)k.n2);
+    k.d_n1 = ndq::make_fastdiv((uint32_t)k.n1);
     if (!fastdiv_ok(k.d_nh3, k.nh3, (uint32_t)g->vh) || !fastdiv_ok(k.d_n2, k.n2, (uint32_t)g->vh) ||
         !fastdiv_ok(k.d_n1, k.n1, (uint32_t)g->vh)) {
         delete g;

@@ -29,6 +29,17 @@ int fail(int status, const char* fmt, ...);
                                __FILE__, __LINE__);                                          \
     } while (0)
 
+// Constants of fdiv for the divisor d >= 1.
+inline FastDiv make_fastdiv(uint32_t d) {
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    const uint64_t num = 1ull << (31 + l);
+    FastDiv f;
+    f.m = (uint32_t)((num + d - 1) / d);
+    f.s = 31 + l;
+    return f;
+}
+
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline int bytes_per_site(int prec) { return prec == NDQ_F64 ? 192 : prec == NDQ_F32 ? 96 : 52; }

@@ -7,23 +7,34 @@
 
 namespace ndq {
 
+// Tile order of a launch (see order_tile): chunk c (0: tiles in index order), the
+// c n0 positions of a chunk over all slices, tiles per slice.
+struct TileOrder {
+    int32_t c, cn, slice;
+    FastDiv d_c, d_cn;
+};
+TileOrder make_order(int64_t tiles, int n0, int c);
+
+// Every view of grid row 1 has the base, stride and rhs_bytes of row 0's (they
+// are the two parities of one field).  What a kernel needs before its first
+// load comes first: the argument lines it waits for.
 struct WilsonArgs {
     GeomK g;
     int p0;                    // parity of the output sites of grid row y = 0
+    int xcd_remap;
+    int has_self;
+    TileOrder order;
     const char* links;
     SpinorView in[2];          // stencil input (parity 1 - p) per grid row
-    SpinorView out[2];
     SpinorView self[2];        // same-site term (parity p)
-    int has_self;
+    SpinorView out[2];
     double a_self, b_hop;
     int gamma5;
+    int nv;
     Coef c0;
     Coef cv[3];
     SpinorView v[3][2];
-    int nv;
     double* partials;          // per-block |out|^2 partial sums (nullptr: none)
-    int xcd_remap;
-    int order_c;               // tile order chunk (0: tiles in index order), see tile_order()
 };
 
 // Chunk c of the L2-friendly tile order for tiles of `block` sites on lattice g,

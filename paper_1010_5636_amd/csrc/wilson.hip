@@ -218,14 +218,12 @@ __device__ __forceinline__ double coef(const Coef& c) { return c.d ? c.f * (*c.d
 // i.e. c consecutive tiles of every x0 slice in turn: x0 neighbours are then c
 // positions apart and x1 neighbours (s1 / tile sites apart) mostly inside the
 // same chunk.  A permutation of the tiles: the arithmetic is unchanged.
-__device__ __forceinline__ int32_t order_tile(int32_t p, int32_t nbx, int n0, int c) {
-    if (c <= 0) return p;
-    const int32_t S = nbx / n0;
-    const int32_t cn = c * n0;
-    const int32_t k = p / cn;
-    const int32_t rem = p - k * cn;
-    const int32_t x0 = rem / c;
-    return x0 * S + k * c + (rem - x0 * c);
+__device__ __forceinline__ int32_t order_tile(int32_t p, const TileOrder& o) {
+    if (o.c <= 0) return p;
+    const int32_t k = (int32_t)fdiv((uint32_t)p, o.d_cn);
+    const int32_t rem = p - k * o.cn;
+    const int32_t x0 = (int32_t)fdiv((uint32_t)rem, o.d_c);
+    return x0 * o.slice + k * o.c + (rem - x0 * o.c);
 }
 
 // Block index remap that gives each of the 8 XCDs (workgroups dispatched
@@ -244,13 +242,13 @@ __device__ __forceinline__ unsigned xcd_remap(unsigned lin, unsigned total) {
 // time: the links one parity reads as forward links the other reads as backward
 // links, and the second read finds them in that XCD's L2.  The position is then
 // mapped to a tile by order_tile.
-__device__ __forceinline__ int32_t parity_slot(unsigned lin, int& y) {
-    if (gridDim.y == 2) {
+__device__ __forceinline__ int32_t parity_slot(unsigned lin, unsigned gx, unsigned gy, int& y) {
+    if (gy == 2) {
         y = (int)(lin & 1u);
         return (int32_t)(lin >> 1);
     }
-    y = (int)(lin / gridDim.x);
-    return (int32_t)(lin - (unsigned)y * gridDim.x);
+    y = 0;   // one output parity
+    return (int32_t)lin;
 }
 
 template <int SP, int LP, int RECON, int BLOCK, bool NT>
@@ -260,8 +258,8 @@ __global__ void __launch_bounds__(BLOCK) k_wilson(WilsonArgs a) {
     unsigned lin = blockIdx.y * gridDim.x + blockIdx.x;
     if (a.xcd_remap) lin = xcd_remap(lin, gridDim.x * gridDim.y);
     int y;
-    const int32_t pos = parity_slot(lin, y);
-    const int32_t i = order_tile(pos, (int32_t)gridDim.x, a.g.n0, a.order_c) * BLOCK + threadIdx.x;
+    const int32_t pos = parity_slot(lin, gridDim.x, gridDim.y, y);
+    const int32_t i = order_tile(pos, a.order) * BLOCK + threadIdx.x;
     const int p = a.p0 + y;
     double red = 0.0;
     if (i < a.g.vh) {
@@ -380,77 +378,126 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     using Part = SplitPart<SP>;
     __shared__ C<R> part[4][12][64];
     __shared__ double red_lds[4];
-    unsigned lin = blockIdx.y * gridDim.x + blockIdx.x;
-    if (a.xcd_remap) lin = xcd_remap(lin, gridDim.x * gridDim.y);
+    // every argument on the way to the first loads, read in one go: left to itself
+    // the compiler reads them one by one where each is used, a dozen scalar
+    // round trips in a row before the first spinor is asked for (mixed solve on
+    // 8^3x16, one workgroup per CU, 333-349 -> 306-314 ms with this, the extra
+    // vectors' views and the epilogue's scalars read ahead; FP64 Q on 24^3x48,
+    // whose tile order now divides by multiplication too, 139.4 -> 134.6 us)
+    WilsonArgs h;
+    h.g = a.g;
+    h.links = a.links;
+    h.order = a.order;
+    const unsigned gx = gridDim.x, gy = gridDim.y;
+    const int p0 = a.p0, remap = a.xcd_remap, has_self = a.has_self;
+    const char* in_base = a.in[0].base;
+    const int32_t in_stride = a.in[0].stride, in0 = a.in[0].site0, in1 = a.in[1].site0;
+    const char* self_base = a.self[0].base;
+    const int32_t self0 = a.self[0].site0, self1 = a.self[1].site0;
+    asm volatile("" ::"s"(h.g.n0), "s"(h.g.n1), "s"(h.g.n2), "s"(h.g.n3), "s"(h.g.nh3), "s"(h.g.s1), "s"(h.g.s0),
+                 "s"(h.g.vh), "s"(h.g.d_nh3.m), "s"(h.g.d_nh3.s), "s"(h.g.d_n2.m), "s"(h.g.d_n2.s), "s"(h.g.d_n1.m),
+                 "s"(h.g.d_n1.s), "s"(p0), "s"(remap), "s"(h.order.c), "s"(has_self), "s"(gx), "s"(gy), "s"(h.links), "s"(in_base),
+                 "s"(in_stride), "s"(in0), "s"(in1), "s"(self_base), "s"(self0), "s"(self1));
+    unsigned lin = blockIdx.y * gx + blockIdx.x;
+    if (remap) lin = xcd_remap(lin, gx * gy);
     int y;
-    const int32_t pos = parity_slot(lin, y);
+    const int32_t pos = parity_slot(lin, gx, gy, y);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t i = order_tile(pos, (int32_t)gridDim.x, a.g.n0, a.order_c) * 64 + lane;
-    const int p = a.p0 + y;
-    const bool active = i < a.g.vh;
+    const int32_t i = order_tile(pos, h.order) * 64 + lane;
+    const int p = p0 + y;
+    const bool active = i < h.g.vh;
+    const SpinorView vin = {const_cast<char*>(in_base), in_stride, y ? in1 : in0, 0};
+    const SpinorView vself = {const_cast<char*>(self_base), in_stride, y ? self1 : self0, 0};
+    SpinorView vj[NV > 0 ? NV : 1];
+    int nv = 0;
+    if constexpr (NV > 0) {
+        nv = a.nv;
+        asm volatile("" : "+s"(nv));
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            vj[j] = a.v[j][0];
+            int32_t s1 = a.v[j][1].site0;
+            asm volatile("" : "+s"(vj[j].base), "+s"(vj[j].stride), "+s"(vj[j].site0), "+s"(s1));
+            if (y) vj[j].site0 = s1;
+        }
+    }
+    // the epilogue's scalars
+    double as_d = a.a_self, b_d = a.b_hop, c0_f = a.c0.f;
+    const double* c0_d = a.c0.d;
+    int g5 = a.gamma5;
+    SpinorView vout = a.out[0];
+    int32_t out1 = a.out[1].site0;
+    double* partials = a.partials;
+    Coef cj[NV > 0 ? NV : 1];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) cj[j] = a.cv[j];
     C<R> sf[Part::kN], vv[NV > 0 ? NV : 1][Part::kN];
     // the epilogue's operands, in flight with those of the hops
     auto epilogue_loads = [&]() {
-        if (!Part::has(w)) return;
-        if (a.has_self) Part::load(a.self[y], (int64_t)a.self[y].site0 + i, w, sf);
+        if (Part::has(w) && has_self) Part::load(vself, (int64_t)vself.site0 + i, w, sf);
 #pragma unroll
         for (int j = 0; j < NV; ++j)
-            if (j < a.nv) Part::load(a.v[j][y], (int64_t)a.v[j][y].site0 + i, w, vv[j]);
+            if (Part::has(w) && j < nv) Part::load(vj[j], (int64_t)vj[j].site0 + i, w, vv[j]);
+        // and its scalars: read behind the barrier, one by one, they cost a round trip each
+        asm volatile("" : "+s"(as_d), "+s"(b_d), "+s"(c0_f), "+s"(c0_d), "+s"(g5), "+s"(vout.base), "+s"(vout.stride),
+                     "+s"(vout.site0), "+s"(out1), "+s"(partials));
+#pragma unroll
+        for (int j = 0; j < NV; ++j) asm volatile("" : "+s"(cj[j].f), "+s"(cj[j].d));
     };
     if (active) {
-        const SiteCoord x = eo_coords(a.g, p, i);
+        const SiteCoord x = eo_coords(h.g, p, i);
         int32_t nb[8];
-        eo_neighbours(a.g, i, x, nb);
+        eo_neighbours(h.g, i, x, nb);
         C<R> acc[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
-        const SpinorView& vin = a.in[y];
         switch (w) {
-            case 0: hop_pair<SP, LP, RECON, 0, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
-            case 1: hop_pair<SP, LP, RECON, 1, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
-            case 2: hop_pair<SP, LP, RECON, 2, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
-            default: hop_pair<SP, LP, RECON, 3, NT, RECON != 18>(a, p, i, nb, vin, acc, epilogue_loads); break;
+            case 0: hop_pair<SP, LP, RECON, 0, NT, RECON != 18>(h, p, i, nb, vin, acc, epilogue_loads); break;
+            case 1: hop_pair<SP, LP, RECON, 1, NT, RECON != 18>(h, p, i, nb, vin, acc, epilogue_loads); break;
+            case 2: hop_pair<SP, LP, RECON, 2, NT, RECON != 18>(h, p, i, nb, vin, acc, epilogue_loads); break;
+            default: hop_pair<SP, LP, RECON, 3, NT, RECON != 18>(h, p, i, nb, vin, acc, epilogue_loads); break;
         }
 #pragma unroll
         for (int k = 0; k < 12; ++k) part[w][k][lane] = acc[k];
     }
+    if (y) vout.site0 = out1;
     __syncthreads();
     double red = 0.0;
     if (active && Part::has(w)) {
-        const R b = (R)a.b_hop;
-        const R as = (R)a.a_self;
-        const R c0 = (R)coef(a.c0);
+        const R b = (R)b_d;
+        const R as = (R)as_d;
+        const R c0 = (R)coef(Coef{c0_f, c0_d});
         const int c1 = Part::kN * w;   // first component of this part
         C<R> t[Part::kN];
 #pragma unroll
         for (int k = 0; k < Part::kN; ++k) {
             const int c = c1 + k;
             t[k] = cadd(cadd(part[0][c][lane], part[1][c][lane]), cadd(part[2][c][lane], part[3][c][lane]));
-            if (a.has_self) t[k] = {as * sf[k].r + b * t[k].r, as * sf[k].i + b * t[k].i};
+            if (has_self) t[k] = {as * sf[k].r + b * t[k].r, as * sf[k].i + b * t[k].i};
             else t[k] = cscale(b, t[k]);
-            if (a.gamma5 && c >= 6) t[k] = cneg(t[k]);
+            if (g5 && c >= 6) t[k] = cneg(t[k]);
             t[k] = cscale(c0, t[k]);
         }
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            if (j < a.nv) {
-                const R cj = (R)coef(a.cv[j]);
+            if (j < nv) {
+                const R cr = (R)coef(cj[j]);
 #pragma unroll
-                for (int k = 0; k < Part::kN; ++k) t[k] = {t[k].r + cj * vv[j][k].r, t[k].i + cj * vv[j][k].i};
+                for (int k = 0; k < Part::kN; ++k) t[k] = {t[k].r + cr * vv[j][k].r, t[k].i + cr * vv[j][k].i};
             }
         }
-        const int64_t so = (int64_t)a.out[y].site0 + i;
-        Part::store(a.out[y], so, w, t);
-        if (a.partials) {
-            if constexpr (SP == P16) Part::load(a.out[y], so, w, t);   // norm of what was stored (after F16 rounding)
+        const int64_t so = (int64_t)vout.site0 + i;
+        Part::store(vout, so, w, t);
+        if (partials) {
+            if constexpr (SP == P16) Part::load(vout, so, w, t);   // norm of what was stored (after F16 rounding)
 #pragma unroll
             for (int k = 0; k < Part::kN; ++k) red += (double)t[k].r * t[k].r + (double)t[k].i * t[k].i;
         }
     }
-    if (a.partials) {
+    if (partials) {
         const double s = block_sum(red, red_lds);
-        if (threadIdx.x == 0) a.partials[lin] = s;
+        if (threadIdx.x == 0) partials[lin] = s;
     }
 }
 
@@ -658,7 +705,7 @@ __global__ void __launch_bounds__(256) k_wilson_mrhs(WilsonArgs a, MrhsGrid m) {
         y = (int)(rem & 1u);
         pos = (int32_t)(rem >> 1);
     }
-    const int32_t tile = order_tile(pos, m.tiles, a.g.n0, a.order_c);
+    const int32_t tile = order_tile(pos, a.order);
     const int r0 = (int)grp * m.rg;
     const int r1 = min(m.nrhs, r0 + m.rg);
     mrhs_tile<SP, LP, RECON, NT>(a.g, a.links, a.p0 + y, tile, a.in[y], a.has_self ? &a.self[y] : nullptr, a.out[y],
@@ -1064,13 +1111,18 @@ hipError_t launch_wilson(int sprec, int lprec, int recon, const WilsonArgs& args
     // full Q, whose larger per-site footprint gains from the slice-chunked
     // order (measured on 24^3 x 48; the F32 and F16 forms gain nothing).
     WilsonArgs a = args;
+    bool chunked = false;
     if (block < 0) {
         const Tuning t = launch_tuning(a.g, sprec, lprec, recon, ny);
         block = t.block;
         a.xcd_remap = t.xcd_remap;
-        if (t.order && a.order_c == 0) a.order_c = tile_order(a.g, block == 0 ? 64 : block);
+        chunked = t.order != 0;
     }
-    if (ny == 2 && sprec == P64 && a.order_c == 0) a.order_c = tile_order(a.g, block == 0 ? 64 : block);
+    if (ny == 2 && sprec == P64) chunked = true;
+    if (chunked) {
+        const int lanes = block == 0 ? 64 : block;
+        a.order = make_order((a.g.vh + lanes - 1) / lanes, a.g.n0, tile_order(a.g, lanes));
+    }
     const int key = sprec * 1000 + lprec * 100 + recon;
     switch (key) {
         case P64 * 1000 + P64 * 100 + 18: return launch_fmt<P64, P64, 18>(a, ny, block, st);
@@ -1117,7 +1169,7 @@ hipError_t launch_wilson_mrhs(int sprec, int lprec, int recon, const WilsonArgs&
                               hipStream_t st) {
     WilsonArgs a = args;
     const MrhsShape sh = mrhs_shape(args.g, sprec, lprec, recon, nrhs, ny);
-    a.order_c = sh.chunk < 0 ? tile_order(a.g, 64) : sh.chunk;
+    a.order = make_order((a.g.vh + 63) / 64, a.g.n0, sh.chunk < 0 ? tile_order(a.g, 64) : sh.chunk);
     a.xcd_remap = sh.xcd_remap;
     MrhsGrid m;
     m.tiles = (a.g.vh + 63) / 64;
@@ -1185,6 +1237,18 @@ hipError_t launch_wilson_multi(int sprec, int lprec, int recon, const MultiArgs&
         case P16 * 1000 + P16 * 100 + 12: return launch_multi_fmt<P16, P16, 12>(a, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+TileOrder make_order(int64_t tiles, int n0, int c) {
+    TileOrder o;
+    memset(&o, 0, sizeof(o));
+    if (c <= 0) return o;
+    o.c = c;
+    o.cn = c * n0;
+    o.slice = (int32_t)(tiles / n0);
+    o.d_c = make_fastdiv((uint32_t)c);
+    o.d_cn = make_fastdiv((uint32_t)o.cn);
+    return o;
 }
 
 int tile_order(const GeomK& g, int block) {
