@@ -484,13 +484,13 @@ __global__ void __launch_bounds__(kBlock) k_phase_copy(SpinorView src, SpinorVie
 //
 // A workgroup takes one chunk of sites and stages K elements (G components of
 // S = K / G sites, G the components in a 16-byte word of B) of every row of A
-// and B in LDS, so that each field is read once and in runs of 16 S bytes; the
-// next stage is in flight in registers meanwhile.  A wavefront accumulates one
-// 16-row tile of G against up to NTJ 16-column tiles with
+// and B in LDS, so that each field is read once and in runs of 16 S bytes; two
+// buffers in turn, and the stage after the next is in flight in registers.  A wavefront accumulates one
+// 16-row tile of G against the NTJ 16-column tiles with
 // v_mfma_f64_16x16x4f64: lane l supplies A_{16 ti + l%16} and B_{16 tj + l%16}
 // at element e + l/16, so each instruction adds four elements' products; real
 // and imaginary parts take four real products (ar br + ai bi, ar bi - ai br).
-// Fewer than 3 row tiles leave wavefronts over: kp of them then share a row
+// Fewer than 3 row tiles leave wavefronts over: KP of them then share a row
 // tile, each with its part of the stage and its own partial tile.  The
 // accumulator lane l, element r holds row 4r + l/16, column l%16.  Partial tiles
 // are summed in a fixed order by k_gram_reduce.  Rows of a tile past na or nb
@@ -499,7 +499,9 @@ __global__ void __launch_bounds__(kBlock) k_phase_copy(SpinorView src, SpinorVie
 // Bound by the FP64 matrix cores for large blocks and by HBM for small ones.
 // Measured, 60 x 60 FP64 fields on 24^3x48 (15.3 GB, 229 Gflop): 11.9 ms when
 // every wavefront loaded its operands from memory itself (16 fields x 64 bytes
-// per instruction, each field once per row tile through L1), 6.0 ms here.
+// per instruction, each field once per row tile through L1), 6.0 ms with one LDS
+// buffer and the operands of a step read as they are needed, 4.5 ms here (57 of the
+// 73 TFLOP/s a large FP64 product reaches, padding to 64 x 64 counted).
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 // FP64 value of the g-th complex component in a 16-byte word of a packed field.
@@ -519,18 +521,18 @@ __device__ __forceinline__ double2 word_comp(const uint4& w, float scale, int g)
 
 constexpr int kGramLoads = 4;   // 16-byte words of A, and of B, per lane and stage
 
-template <int PB, int K, int NTJ>
-__global__ void __launch_bounds__(256) k_gram(const char* __restrict__ A, int na, const char* __restrict__ B, int nb,
-                                              int64_t vb, int64_t vbB, int32_t V, int32_t sites_per_chunk, int kp,
+template <int PB, int K, int NTJ, int KP>
+__global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int na, const char* __restrict__ B, int nb,
+                                              int64_t vb, int64_t vbB, int32_t V, int32_t sites_per_chunk,
                                               double* __restrict__ partials) {
     constexpr int G = PB == P64 ? 1 : PB == P32 ? 2 : 4;
     constexpr int S = K / G;
     constexpr int kRow = K + 1;   // odd row stride: the 16 rows of a tile fall on different banks
-    extern __shared__ double2 gram_lds[];   // [na + nb][kRow]
+    extern __shared__ double2 gram_lds[];   // [2][na + nb][kRow]
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int t = lane & 15, kk = lane >> 4;
-    const int nti = (na + 15) / 16, ntj = (nb + 15) / 16;
+    const int nti = (na + 15) / 16;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ti = wave % nti, part = wave / nti;
     const int32_t s0 = (int32_t)min((int64_t)V, (int64_t)blockIdx.x * sites_per_chunk);
@@ -557,16 +559,17 @@ __global__ void __launch_bounds__(256) k_gram(const char* __restrict__ A, int na
             }
         }
     };
-    auto stage = [&]() {
+    const int half = (na + nb) * kRow;
+    auto stage = [&](double2* dst) {
 #pragma unroll
         for (int n = 0; n < kGramLoads; ++n) {
             const int ea = n * 256 + tid, ra_row = ea / K, e = ea % K;
-            if (ra_row < na) gram_lds[ra_row * kRow + e] = word_comp<P64>(ra[n], 0.f, 0);
+            if (ra_row < na) dst[ra_row * kRow + e] = word_comp<P64>(ra[n], 0.f, 0);
             const int eb = n * 256 + tid, rb_row = eb / S;
             if (rb_row < nb) {
 #pragma unroll
                 for (int g = 0; g < G; ++g)
-                    gram_lds[(na + rb_row) * kRow + g * S + eb % S] = word_comp<PB>(rb[n], rs[n], g);
+                    dst[(na + rb_row) * kRow + g * S + eb % S] = word_comp<PB>(rb[n], rs[n], g);
             }
         }
     };
@@ -576,51 +579,72 @@ __global__ void __launch_bounds__(256) k_gram(const char* __restrict__ A, int na
         re[q] = v4d{0.0, 0.0, 0.0, 0.0};
         im[q] = v4d{0.0, 0.0, 0.0, 0.0};
     }
-    const double2* la = gram_lds + min(ti * 16 + t, na - 1) * kRow + kk;
-    const double2* lb[NTJ];
+    const int oa = min(ti * 16 + t, na - 1) * kRow + kk;
+    int ob[NTJ];
 #pragma unroll
-    for (int q = 0; q < NTJ; ++q) lb[q] = gram_lds + (na + min(q * 16 + t, nb - 1)) * kRow + kk;
+    for (int q = 0; q < NTJ; ++q) ob[q] = (na + min(q * 16 + t, nb - 1)) * kRow + kk;
+    constexpr int kGroups = 12 / G;
+    const int32_t nstages = s0 < s1 ? kGroups * ((s1 - s0 + S - 1) / S) : 0;
     int cg = 0;
     int32_t s = s0;
-    if (s0 < s1) load(0, s0);
-    while (s0 < s1 && cg < 12 / G) {
-        __syncthreads();   // the previous stage has been read
-        stage();
+    auto next = [&]() {   // the stage after (cg, s) into registers, nothing past the last
         s += S;
         if (s >= s1) {
             s = s0;
             ++cg;
         }
-        if (cg < 12 / G) load(cg, s);
-        __syncthreads();
-        if (part < kp) {
-            for (int e = 4 * part; e < K; e += 4 * kp) {
-                const double2 a = la[e];
+        if (cg < kGroups) load(cg, s);
+    };
+    if (nstages > 0) {
+        load(0, s0);
+        stage(gram_lds);
+        next();
+    }
+    for (int32_t it = 0; it < nstages; ++it) {
+        __syncthreads();   // stage it is in LDS, and stage it - 1 has been read
+        const double2* src = gram_lds + (it & 1) * half;
+        if (it + 1 < nstages) {
+            stage(gram_lds + ((it + 1) & 1) * half);
+            next();
+        }
+        if (part < KP) {
+            // the operands of a step are read while the one before it multiplies
+            constexpr int kSteps = K / (4 * KP);
+            double2 x[2], y[2][NTJ];
+            auto fetch = [&](int n) {
+                const int e = 4 * (part + n * KP);
+                x[n & 1] = src[oa + e];
+#pragma unroll
+                for (int q = 0; q < NTJ; ++q)
+                    y[n & 1][q] = src[ob[q] + e];
+            };
+            fetch(0);
+#pragma unroll
+            for (int n = 0; n < kSteps; ++n) {
+                if (n + 1 < kSteps) fetch(n + 1);
+                const double2 a = x[n & 1];
 #pragma unroll
                 for (int q = 0; q < NTJ; ++q) {
-                    if (q < ntj) {
-                        const double2 b = lb[q][e];
-                        re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[q], 0, 0, 0);
-                        im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[q], 0, 0, 0);
-                        re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[q], 0, 0, 0);
-                        im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[q], 0, 0, 0);
-                    }
+                    const double2 b = y[n & 1][q];
+                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[q], 0, 0, 0);
+                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[q], 0, 0, 0);
+                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[q], 0, 0, 0);
+                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[q], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    if (part >= kp) return;
-    const int NI = 16 * nti, NJ = 16 * ntj;
-    double2* out = reinterpret_cast<double2*>(partials) + ((int64_t)blockIdx.x * kp + part) * NI * NJ;
+    if (part >= KP) return;
+    const int NI = 16 * nti, NJ = 16 * NTJ;
+    double2* out = reinterpret_cast<double2*>(partials) + ((int64_t)blockIdx.x * KP + part) * NI * NJ;
 #pragma unroll
     for (int q = 0; q < NTJ; ++q) {
-        if (q < ntj) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = ti * 16 + 4 * r + kk;
-                const int j = q * 16 + t;
-                out[(int64_t)i * NJ + j] = make_double2(re[q][r], im[q][r]);
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int i = ti * 16 + 4 * r + kk;
+            const int j = q * 16 + t;
+            out[(int64_t)i * NJ + j] = make_double2(re[q][r], im[q][r]);
         }
     }
 }
@@ -841,31 +865,58 @@ int gram_chunks(const ndq_geom* g, int na, int nb) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(4096, cap), (g->volume + 63) / 64));
 }
 
-// A stage holds K elements of every row; a lane stages at most kGramLoads words
-// of A and of B, so K = 16 serves any block, and smaller blocks take longer
-// runs (16 S bytes of each field) with the fewer accumulators they need.
-template <int PB, int K, int NTJ>
-hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
-                         double* partials, hipStream_t st) {
+// Wavefronts that share a row tile: all four for up to 16 rows, two for up to 32.
+int gram_kp(int na, int nw) {
     const int nti = (na + 15) / 16;
     int kp = nti == 1 ? 4 : nti == 2 ? 2 : 1;
     while (kp > nw) kp >>= 1;
-    const int chunks = nw / kp;
+    return kp;
+}
+
+// A stage holds K elements of every row; a lane stages at most kGramLoads words
+// of A and of B, so K = 16 serves any block, and smaller blocks take longer
+// runs (16 S bytes of each field) with the fewer accumulators they need.
+template <int PB, int K, int NTJ, int KP>
+hipError_t launch_gram_kp(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
+                          double* partials, hipStream_t st) {
+    const int chunks = nw / KP;
     int32_t spc = (V + chunks - 1) / chunks;
     spc = (spc + 63) & ~63;   // whole stages, and runs that start on a cache line
-    const size_t lds = (size_t)(na + nb) * (K + 1) * sizeof(double2);
-    hipLaunchKernelGGL((k_gram<PB, K, NTJ>), dim3(chunks), dim3(256), lds, st, A, na, B, nb, vb, vbB, V, spc, kp,
+    const size_t lds = (size_t)2 * (na + nb) * (K + 1) * sizeof(double2);
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram<PB, K, NTJ, KP>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_gram<PB, K, NTJ, KP>), dim3(chunks), dim3(256), lds, st, A, na, B, nb, vb, vbB, V, spc,
                        partials);
     return hipGetLastError();
+}
+
+template <int PB, int K, int NTJ>
+hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
+                         double* partials, hipStream_t st) {
+    switch (gram_kp(na, nw)) {
+        case 4: return launch_gram_kp<PB, K, NTJ, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+        case 2: return launch_gram_kp<PB, K, NTJ, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+        default: return launch_gram_kp<PB, K, NTJ, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    }
 }
 
 template <int PB>
 hipError_t launch_gram(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
                        double* partials, hipStream_t st) {
     static_assert(64 * 16 <= 256 * kGramLoads, "a stage of 64 rows");
-    if (na <= 16 && nb <= 16) return launch_gram_k<PB, 64, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    if (na <= 32 && nb <= 32) return launch_gram_k<PB, 32, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    return launch_gram_k<PB, 16, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    const int ntj = (nb + 15) / 16;
+    if (na <= 16 && ntj == 1) return launch_gram_k<PB, 64, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    if (na <= 32 && ntj == 1) return launch_gram_k<PB, 32, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    if (na <= 32 && ntj == 2) return launch_gram_k<PB, 32, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    switch (ntj) {
+        case 1: return launch_gram_k<PB, 16, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+        case 2: return launch_gram_k<PB, 16, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+        case 3: return launch_gram_k<PB, 16, 3>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+        default: return launch_gram_k<PB, 16, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
+    }
 }
 }  // namespace
 
@@ -890,9 +941,7 @@ int gram_block(const ndq_geom* g, const void* A, int na, const ndq_spinor* B, do
         default: NDQ_HIP(launch_gram<P16>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
     }
     // partial tiles written: the kernel's chunks times the wavefronts sharing a row tile
-    const int nti = (na + 15) / 16;
-    int kp = nti == 1 ? 4 : nti == 2 ? 2 : 1;
-    while (kp > nw) kp >>= 1;
+    const int kp = gram_kp(na, nw);
     hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, nw / kp * kp, G);
     NDQ_HIP(hipGetLastError());
     return NDQ_OK;
