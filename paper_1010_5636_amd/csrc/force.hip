@@ -18,53 +18,41 @@ using namespace ndq;
 
 namespace {
 
-// (1 -+ gamma_mu) psi with the chiral gamma matrices: upper two spins h, lower
-// two from the fixed spin map (the same maps as the stencil's hop functions).
-template <bool MINUS>
-__device__ __forceinline__ void spin_project_full(int mu, const C<double> s[12], C<double> out[12]) {
+// Upper two spins of (1 -+ gamma_mu) s with the chiral gamma matrices, as the
+// stencil's hop functions project.  (1 -+ gamma_mu) is twice a projector, so
+// <chi, (1 -+ gamma_mu) psi> = 1/2 <(1 -+ gamma_mu) chi, (1 -+ gamma_mu) psi>, and
+// the lower spins of both factors repeat the upper ones: the colour matrices H and
+// K are sums over two spins of these.
+template <int MU, bool MINUS>
+__device__ __forceinline__ void spin_project(const C<double> s[12], C<double> h[6]) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const C<double> s0 = s[c], s1 = s[3 + c], s2 = s[6 + c], s3 = s[9 + c];
-        C<double> h0, h1, l2, l3;
-        if (mu == 0) {
-            h0 = MINUS ? cadd(s0, s2) : csub(s0, s2);
-            h1 = MINUS ? cadd(s1, s3) : csub(s1, s3);
-            l2 = MINUS ? h0 : cneg(h0);
-            l3 = MINUS ? h1 : cneg(h1);
-        } else if (mu == 1) {
-            h0 = MINUS ? cadd(s0, cmuli(s3)) : csub(s0, cmuli(s3));
-            h1 = MINUS ? cadd(s1, cmuli(s2)) : csub(s1, cmuli(s2));
-            l2 = MINUS ? cmulmi(h1) : cmuli(h1);
-            l3 = MINUS ? cmulmi(h0) : cmuli(h0);
-        } else if (mu == 2) {
-            h0 = MINUS ? cadd(s0, s3) : csub(s0, s3);
-            h1 = MINUS ? csub(s1, s2) : cadd(s1, s2);
-            l2 = MINUS ? cneg(h1) : h1;
-            l3 = MINUS ? h0 : cneg(h0);
+        C<double> a, b;   // h0 = s0 +- a, h1 = s1 +- b
+        if constexpr (MU == 0) {
+            a = s2;
+            b = s3;
+        } else if constexpr (MU == 1) {
+            a = cmuli(s3);
+            b = cmuli(s2);
+        } else if constexpr (MU == 2) {
+            a = s3;
+            b = cneg(s2);
         } else {
-            h0 = MINUS ? cadd(s0, cmuli(s2)) : csub(s0, cmuli(s2));
-            h1 = MINUS ? csub(s1, cmuli(s3)) : cadd(s1, cmuli(s3));
-            l2 = MINUS ? cmulmi(h0) : cmuli(h0);
-            l3 = MINUS ? cmuli(h1) : cmulmi(h1);
+            a = cmuli(s2);
+            b = cmulmi(s3);
         }
-        out[c] = h0;
-        out[3 + c] = h1;
-        out[6 + c] = l2;
-        out[9 + c] = l3;
+        h[c] = MINUS ? cadd(s0, a) : csub(s0, a);
+        h[3 + c] = MINUS ? cadd(s1, b) : csub(s1, b);
     }
 }
 
-// O_ba = sum_s p_{s b} conj(q_{s a})
-__device__ __forceinline__ void outer(const C<double> p[12], const C<double> q[12], C<double> o[3][3]) {
+// O_ba = sum over the two upper spins of p_{s b} conj(q_{s a})
+__device__ __forceinline__ void outer(const C<double> p[6], const C<double> q[6], C<double> o[3][3]) {
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            C<double> acc = {0.0, 0.0};
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp) acc = cfmac(acc, q[3 * sp + a], p[3 * sp + b]);
-            o[b][a] = acc;
-        }
+        for (int a = 0; a < 3; ++a) o[b][a] = cfmac(cmulc(q[a], p[b]), q[3 + a], p[3 + b]);
 }
 
 struct ForceArgs {
@@ -76,36 +64,39 @@ struct ForceArgs {
     double2* grad;       // [V][4][3][3] complex (lexicographic) or nullptr
 };
 
-// One workgroup per 64 sites of one parity; wavefront w takes direction mu = w,
-// so the four directions of a site read psi(x) and g(x) from the same cache
-// lines at about the same time.
-template <int RECON>
-__global__ void __launch_bounds__(256) k_force(ForceArgs a) {
-    const int p = blockIdx.y;
-    const int mu = threadIdx.x >> 6;
-    const int32_t i = blockIdx.x * 64 + (threadIdx.x & 63);
-    if (i >= a.g.vh) return;
-    const SiteCoord x = eo_coords(a.g, p, i);
-    int32_t nb[8];
-    eo_neighbours(a.g, i, x, nb);
-    C<double> u[3][3];
-    link_load<P64, RECON>(a.links, a.g.vh, p * 4 + mu, i, u);
-    C<double> sx[12], sf[12], gx[12], gf[12];
-    SpinorIO<P64>::load(a.psi[p], (int64_t)a.psi[p].site0 + i, sx);
-    SpinorIO<P64>::load(a.psi[1 - p], (int64_t)a.psi[1 - p].site0 + nb[mu], sf);
-    SpinorIO<P64>::load(a.gv[p], (int64_t)a.gv[p].site0 + i, gx);
-    SpinorIO<P64>::load(a.gv[1 - p], (int64_t)a.gv[1 - p].site0 + nb[mu], gf);
-#pragma unroll
-    for (int k = 6; k < 12; ++k) {   // chi = gamma5 g
-        gx[k] = cneg(gx[k]);
-        gf[k] = cneg(gf[k]);
-    }
-    C<double> hm[12], kp[12];
-    spin_project_full<true>(mu, sf, hm);    // (1 - gamma_mu) psi(x + mu)
-    spin_project_full<false>(mu, sx, kp);   // (1 + gamma_mu) psi(x)
+constexpr double is3 = 0.57735026918962576451;   // 1/sqrt(3)
+
+// U_mu(x) and its force components for the site (p, i) with neighbour nbr = x + mu.
+template <int RECON, int MU>
+__device__ __forceinline__ void link_force(const ForceArgs& a, int p, int32_t i, int32_t nbr, C<double> u[3][3],
+                                           double f[8]) {
     C<double> H[3][3], K[3][3], G[3][3];
-    outer(hm, gx, H);
-    outer(kp, gf, K);
+    {
+        C<double> s[12], c[12], ps[6], pc[6];
+        SpinorIO<P64>::load(a.psi[1 - p], (int64_t)a.psi[1 - p].site0 + nbr, s);
+        SpinorIO<P64>::load(a.gv[p], (int64_t)a.gv[p].site0 + i, c);
+#pragma unroll
+        for (int k = 6; k < 12; ++k) c[k] = cneg(c[k]);   // chi = gamma5 g
+        spin_project<MU, true>(s, ps);    // (1 - gamma_mu) psi(x + mu)
+        spin_project<MU, true>(c, pc);    // (1 - gamma_mu) chi(x)
+        outer(ps, pc, H);
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(H[b][k].r), "+v"(H[b][k].i));
+    }
+    __builtin_amdgcn_sched_barrier(0);   // not all 57 loads at once: their registers halve the wavefronts in flight
+    {
+        C<double> s[12], c[12], ps[6], pc[6];
+        SpinorIO<P64>::load(a.psi[p], (int64_t)a.psi[p].site0 + i, s);
+        SpinorIO<P64>::load(a.gv[1 - p], (int64_t)a.gv[1 - p].site0 + nbr, c);
+#pragma unroll
+        for (int k = 6; k < 12; ++k) c[k] = cneg(c[k]);
+        spin_project<MU, false>(s, ps);   // (1 + gamma_mu) psi(x)
+        spin_project<MU, false>(c, pc);   // (1 + gamma_mu) chi(x + mu)
+        outer(ps, pc, K);
+    }
+    link_load<P64, RECON>(a.links, a.g.vh, p * 4 + MU, i, u);
     // G = U H - K U^H
 #pragma unroll
     for (int r = 0; r < 3; ++r)
@@ -120,8 +111,6 @@ __global__ void __launch_bounds__(256) k_force(ForceArgs a) {
             G[r][c] = acc;
         }
     // F^a = 1/2 Im tr(T_a G), T_a = lambda_a / 2 (Gell-Mann)
-    double f[8];
-    const double is3 = 0.57735026918962576451;   // 1/sqrt(3)
     f[0] = 0.25 * (G[1][0].i + G[0][1].i);                       // lambda_1: (0,1),(1,0) = 1
     f[1] = 0.25 * (G[0][1].r - G[1][0].r);                       // lambda_2: (0,1) = -i, (1,0) = i
     f[2] = 0.25 * (G[0][0].i - G[1][1].i);                       // lambda_3
@@ -130,10 +119,48 @@ __global__ void __launch_bounds__(256) k_force(ForceArgs a) {
     f[5] = 0.25 * (G[2][1].i + G[1][2].i);                       // lambda_6
     f[6] = 0.25 * (G[1][2].r - G[2][1].r);                       // lambda_7
     f[7] = 0.25 * is3 * (G[0][0].i + G[1][1].i - 2.0 * G[2][2].i);  // lambda_8
-    const int64_t lex = 2 * (int64_t)i + (x.x3 & 1);
+}
+
+// One workgroup per 64 sites of one parity; wavefront w takes direction mu = w,
+// so the four directions of a site read psi(x) and g(x) from the same cache
+// lines at about the same time.  A site's outputs are 576 (gradient) and 256
+// (force) contiguous bytes from four wavefronts: they meet in LDS and leave as
+// whole lines.  Bound by HBM: 1216 bytes per site with 18-real links and the
+// force, 1536 with the gradient; the gradient on 16^3x32 61 us with each lane
+// storing its own 16-byte words and full four-spin products, 55 us here.
+template <int RECON>
+__global__ void __launch_bounds__(256) k_force(ForceArgs a) {
+    constexpr int kRow = 37;   // double2 per site: 36 and one that spreads the banks
+    __shared__ double2 out[64 * kRow];
+    __shared__ int32_t site_lex[64];
+    const int p = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t it = blockIdx.x * 64 + lane;
+    const bool active = it < a.g.vh;
+    const int32_t i = active ? it : a.g.vh - 1;   // lanes past the end repeat the last site and store nothing
+    const int nsites = min(64, a.g.vh - (int32_t)blockIdx.x * 64);
+    const SiteCoord x = eo_coords(a.g, p, i);
+    int32_t nb[8];
+    eo_neighbours(a.g, i, x, nb);
+    C<double> u[3][3];
+    double f[8];
+    switch (mu) {
+        case 0: link_force<RECON, 0>(a, p, i, nb[0], u, f); break;
+        case 1: link_force<RECON, 1>(a, p, i, nb[1], u, f); break;
+        case 2: link_force<RECON, 2>(a, p, i, nb[2], u, f); break;
+        default: link_force<RECON, 3>(a, p, i, nb[3], u, f); break;
+    }
+    if (mu == 0) site_lex[lane] = 2 * i + (x.x3 & 1);
     if (a.force) {
+        double* row = reinterpret_cast<double*>(out + lane * kRow) + mu * 8;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a.force[(lex * 4 + mu) * 8 + k] = f[k];
+        for (int k = 0; k < 8; ++k) row[k] = f[k];
+        __syncthreads();
+        double2* dst = reinterpret_cast<double2*>(a.force);
+        for (int e = threadIdx.x; e < nsites * 16; e += 256)
+            dst[(int64_t)site_lex[e >> 4] * 16 + (e & 15)] = out[(e >> 4) * kRow + (e & 15)];
+        if (a.grad) __syncthreads();   // before the gradient takes the rows
     }
     if (a.grad) {
         // 2 i sum_a f_a T_a U = i (sum_a f_a lambda_a) U
@@ -147,7 +174,7 @@ __global__ void __launch_bounds__(256) k_force(ForceArgs a) {
         Lm[2][0] = {f[3], f[4]};
         Lm[1][2] = {f[5], -f[6]};
         Lm[2][1] = {f[5], f[6]};
-        double2* dst = a.grad + (lex * 4 + mu) * 9;
+        double2* row = out + lane * kRow + mu * 9;
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -156,8 +183,13 @@ __global__ void __launch_bounds__(256) k_force(ForceArgs a) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) acc = cfma(acc, Lm[r][k], u[k][c]);
                 const C<double> v = cmuli(acc);
-                dst[3 * r + c] = make_double2(v.r, v.i);
+                row[3 * r + c] = make_double2(v.r, v.i);
             }
+        __syncthreads();
+        for (int e = threadIdx.x; e < nsites * 36; e += 256) {
+            const int s = e / 36, k = e - 36 * s;
+            a.grad[(int64_t)site_lex[s] * 36 + k] = out[s * kRow + k];
+        }
     }
 }
 
