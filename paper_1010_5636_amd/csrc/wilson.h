@@ -66,11 +66,13 @@ struct MultiArgs {
 struct Tuning {
     int block = 0;
     int xcd_remap = 1;
-    int order = 0;    // 1: tiles in the slice-chunked order of tile_order (autotuner only)
+    int order = -1;   // 1: tiles in the slice-chunked order of tile_order, 0: index order, -1: by
+                      // default_order (launch_tuning puts 0 or 1 in its place)
 };
 // Per storage format (spinor precision, link precision, recon index 0/1/2 for
 // 18/12/8); set by ndq_set_launch / ndq_set_launch_for (the autotuner).
 Tuning& tuning(int sprec, int lprec, int recon);
+int default_order(const GeomK& g, int sprec, int ny);
 // The shape of one lattice and number of output parities (1: dslash, 2: Q):
 // the autotuner's choice for that lattice if it made one, else the format's.
 Tuning launch_tuning(const GeomK& g, int sprec, int lprec, int recon, int ny);

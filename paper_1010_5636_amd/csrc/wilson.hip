@@ -1107,19 +1107,15 @@ int wilson_blocks(const ndq_geom* g, int block, int ny) {
 
 hipError_t launch_wilson(int sprec, int lprec, int recon, const WilsonArgs& args, int ny, int block,
                          hipStream_t st) {
-    // Single-right-hand-side kernels keep the index order, except the FP64
-    // full Q, whose larger per-site footprint gains from the slice-chunked
-    // order (measured on 24^3 x 48; the F32 and F16 forms gain nothing).
     WilsonArgs a = args;
-    bool chunked = false;
+    int order = default_order(a.g, sprec, ny);
     if (block < 0) {
         const Tuning t = launch_tuning(a.g, sprec, lprec, recon, ny);
         block = t.block;
         a.xcd_remap = t.xcd_remap;
-        chunked = t.order != 0;
+        order = t.order;
     }
-    if (ny == 2 && sprec == P64) chunked = true;
-    if (chunked) {
+    if (order) {
         const int lanes = block == 0 ? 64 : block;
         a.order = make_order((a.g.vh + lanes - 1) / lanes, a.g.n0, tile_order(a.g, lanes));
     }
