@@ -502,21 +502,26 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
 }
 
 // Links of a multi-right-hand-side tile in LDS, per direction a block of
-// planes of 64 sites (lane l touches consecutive words).  F32/F16 links are
-// decoded to 18 reals once per tile (the 12- and 8-real reconstructions then
-// run once per link, not once per right-hand side); FP64 links stay in their
-// stored words and are decoded per right-hand side, which keeps the LDS of a
-// 12-real FP64 tile at 48 KiB.
+// planes of 64 sites (lane l touches consecutive words).  F32/F16 links and the
+// 8-real FP64 ones are decoded to 18 reals once per tile (the reconstructions
+// then run once per link, not once per right-hand side).  For 8 FP64 reals, sine,
+// cosine, square roots and a division per link, that is most of the work, and in
+// the field loop it spilled (480 bytes a lane, one wavefront per SIMD): 12 fields
+// on 24^3x48 4432 -> 1175 us, 8 on 16^3x32 474 -> 151 us, the same bits, with 72
+// KiB of LDS and the two wavefronts per SIMD that the registers allow.  12- and
+// 18-real FP64 links stay in their stored words and are decoded per right-hand
+// side: a 12-real tile needs 48 KiB, and its cross products cost less than reading
+// the third row back (12 fields 1153 us against 1178, 60 fields 5.70 against 5.82 ms).
 template <int LP, int RECON>
 struct StagedLinks {
     using LR = typename LinkReal<LP>::R;
-    static constexpr bool kDecoded = LP != P64;
-    static constexpr int kWords = kDecoded ? 18 : LinkFmt<LP, RECON>::kWords;
+    static constexpr bool kDecoded = LP != P64 || RECON == 8;
+    static constexpr int kWords = kDecoded ? 18 * (int)(sizeof(LR) / 4) : LinkFmt<LP, RECON>::kWords;
     __device__ static __forceinline__ void put(uint32_t* lw, int dir, int lane, const uint32_t words[]) {
         if constexpr (kDecoded) {
             C<LR> u[3][3];
             link_decode<LP, RECON>(words, u);
-            float* d = reinterpret_cast<float*>(lw) + dir * 18 * 64 + lane;
+            LR* d = reinterpret_cast<LR*>(lw) + dir * 18 * 64 + lane;
 #pragma unroll
             for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -531,7 +536,7 @@ struct StagedLinks {
     }
     __device__ static __forceinline__ void get(const uint32_t* lw, int dir, int lane, C<LR> u[3][3]) {
         if constexpr (kDecoded) {
-            const float* d = reinterpret_cast<const float*>(lw) + dir * 18 * 64 + lane;
+            const LR* d = reinterpret_cast<const LR*>(lw) + dir * 18 * 64 + lane;
 #pragma unroll
             for (int r = 0; r < 3; ++r)
 #pragma unroll
