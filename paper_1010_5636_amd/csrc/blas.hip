@@ -482,26 +482,33 @@ __global__ void __launch_bounds__(kBlock) k_phase_copy(SpinorView src, SpinorVie
 // a tall-skinny product (K = 12 V, at most 64 x 64 outputs), A in FP64, B in
 // F64, F32 or F16 (PB; converted to FP64).
 //
-// A workgroup takes one chunk of sites and stages K elements (G components of
-// S = K / G sites, G the components in a 16-byte word of B) of every row of A
-// and B in LDS, so that each field is read once and in runs of 16 S bytes; two
-// buffers in turn, and the stage after the next is in flight in registers.  A wavefront accumulates one
-// 16-row tile of G against the NTJ 16-column tiles with
-// v_mfma_f64_16x16x4f64: lane l supplies A_{16 ti + l%16} and B_{16 tj + l%16}
-// at element e + l/16, so each instruction adds four elements' products; real
-// and imaginary parts take four real products (ar br + ai bi, ar bi - ai br).
-// Fewer than 3 row tiles leave wavefronts over: KP of them then share a row
-// tile, each with its part of the stage and its own partial tile.  The
-// accumulator lane l, element r holds row 4r + l/16, column l%16.  Partial tiles
-// are summed in a fixed order by k_gram_reduce.  Rows of a tile past na or nb
-// read another row's elements; only outputs nobody reads come of them.
+// A stage is K elements (G components of S = K / G sites, G the components in a
+// 16-byte word of B) of every row of A and B, staged in LDS so that each field is
+// read once and in runs of 16 S bytes; two buffers in turn, and the stage after the
+// next is in flight in registers.  A workgroup takes a run of the stages of all
+// component groups.  A wavefront accumulates NTI 16-row tiles of G against the NTJ
+// 16-column tiles with v_mfma_f64_16x16x4f64: lane l supplies A_{16 ti + l%16} and
+// B_{16 tj + l%16} at element e + l/16, so each instruction adds four elements'
+// products; real and imaginary parts take four real products (ar br + ai bi, ar bi
+// - ai br).  KP wavefronts share a row tile, each with its part of the stage: four
+// where there is one row tile, two of two each where there are two; with three
+// every wavefront takes all of them and a quarter of the stage, as one row tile
+// each leaves the fourth SIMD idle.  Their sums meet in LDS.  The accumulator lane
+// l, element r holds row 4r + l/16, column l%16.  The workgroups' results are
+// summed in a fixed order by k_gram_reduce.  Rows of a tile past na or nb read
+// another row's elements; only outputs nobody reads come of them.
 //
-// Bound by the FP64 matrix cores for large blocks and by HBM for small ones.
-// Measured, 60 x 60 FP64 fields on 24^3x48 (15.3 GB, 229 Gflop): 11.9 ms when
-// every wavefront loaded its operands from memory itself (16 fields x 64 bytes
-// per instruction, each field once per row tile through L1), 6.0 ms with one LDS
-// buffer and the operands of a step read as they are needed, 4.5 ms here (57 of the
-// 73 TFLOP/s a large FP64 product reaches, padding to 64 x 64 counted).
+// Bound by the FP64 matrix cores for large blocks, by HBM for small ones and by
+// the chain of stages on small lattices.  Measured, 60 x 60 FP64 fields on 24^3x48
+// (15.3 GB, 229 Gflop): 11.9 ms when every wavefront loaded its operands from
+// memory itself (16 fields x 64 bytes per instruction, each field once per row tile
+// through L1), 6.0 ms with one LDS buffer and the operands of a step read as they
+// are needed, 4.4 ms here (59 of the 73 TFLOP/s a large FP64 product reaches, padding
+// to 64 x 64 counted).  Three row tiles in all wavefronts, against one each: 33
+// fields 3.7 -> 2.6 ms, 48 fields 4.1 -> 3.0 ms.  Stages of all components shared out,
+// against each workgroup taking all components of its sites and one partial result
+// per wavefront: 8 fields on 8^3x16 54 -> 20 us, 32 fields 85 -> 49 us, 2 on 24^3x48
+// 321 -> 306 us.
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 // FP64 value of the g-th complex component in a 16-byte word of a packed field.
@@ -521,9 +528,9 @@ __device__ __forceinline__ double2 word_comp(const uint4& w, float scale, int g)
 
 constexpr int kGramLoads = 4;   // 16-byte words of A, and of B, per lane and stage
 
-template <int PB, int K, int NTJ, int KP>
+template <int PB, int K, int NTI, int NTJ, int KP>
 __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int na, const char* __restrict__ B, int nb,
-                                              int64_t vb, int64_t vbB, int32_t V, int32_t sites_per_chunk,
+                                              int64_t vb, int64_t vbB, int32_t V,
                                               double* __restrict__ partials) {
     constexpr int G = PB == P64 ? 1 : PB == P32 ? 2 : 4;
     constexpr int S = K / G;
@@ -534,9 +541,13 @@ __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int
     const int t = lane & 15, kk = lane >> 4;
     const int nti = (na + 15) / 16;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ti = wave % nti, part = wave / nti;
-    const int32_t s0 = (int32_t)min((int64_t)V, (int64_t)blockIdx.x * sites_per_chunk);
-    const int32_t s1 = (int32_t)min((int64_t)V, (int64_t)s0 + sites_per_chunk);
+    // NTI = 1: one row tile per wavefront, KP wavefronts per row tile; else all of them
+    const int ti = NTI == 1 ? wave % nti : 0, part = NTI == 1 ? wave / nti : wave;
+    // stages, component groups outermost: this workgroup's share of them
+    constexpr int kGroups = 12 / G;
+    const int32_t spg = (V + S - 1) / S;
+    const int32_t it0 = (int32_t)((int64_t)kGroups * spg * blockIdx.x / gridDim.x);
+    const int32_t nstages = (int32_t)((int64_t)kGroups * spg * (blockIdx.x + 1) / gridDim.x) - it0;
     uint4 ra[kGramLoads], rb[kGramLoads];
     float rs[kGramLoads];
     // stage (component group cg, sites from s) of every row into registers
@@ -546,13 +557,13 @@ __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int
             const int ea = n * 256 + tid, ra_row = ea / K, e = ea % K;
             const int32_t sa = s + e % S;
             ra[n] = make_uint4(0, 0, 0, 0);
-            if (ra_row < na && sa < s1)
+            if (ra_row < na && sa < V)
                 ra[n] = reinterpret_cast<const uint4*>(A + (int64_t)ra_row * vb)[(int64_t)(cg * G + e / S) * V + sa];
             const int eb = n * 256 + tid, rb_row = eb / S;
             const int32_t sb = s + eb % S;
             rb[n] = make_uint4(0, 0, 0, 0);
             rs[n] = 0.f;
-            if (rb_row < nb && sb < s1) {
+            if (rb_row < nb && sb < V) {
                 const char* pb = B + (int64_t)rb_row * vbB;
                 rb[n] = reinterpret_cast<const uint4*>(pb)[(int64_t)cg * V + sb];
                 if constexpr (PB == P16) rs[n] = reinterpret_cast<const float*>(pb + (int64_t)48 * V)[sb];
@@ -573,30 +584,32 @@ __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int
             }
         }
     };
-    v4d re[NTJ], im[NTJ];
+    v4d re[NTI][NTJ], im[NTI][NTJ];
+    int oa[NTI], ob[NTJ];
 #pragma unroll
-    for (int q = 0; q < NTJ; ++q) {
-        re[q] = v4d{0.0, 0.0, 0.0, 0.0};
-        im[q] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < NTI; ++u) {
+#pragma unroll
+        for (int q = 0; q < NTJ; ++q) {
+            re[u][q] = v4d{0.0, 0.0, 0.0, 0.0};
+            im[u][q] = v4d{0.0, 0.0, 0.0, 0.0};
+        }
+        oa[u] = min((ti + u) * 16 + t, na - 1) * kRow + kk;
     }
-    const int oa = min(ti * 16 + t, na - 1) * kRow + kk;
-    int ob[NTJ];
 #pragma unroll
     for (int q = 0; q < NTJ; ++q) ob[q] = (na + min(q * 16 + t, nb - 1)) * kRow + kk;
-    constexpr int kGroups = 12 / G;
-    const int32_t nstages = s0 < s1 ? kGroups * ((s1 - s0 + S - 1) / S) : 0;
-    int cg = 0;
-    int32_t s = s0;
+    int cg = it0 / spg;
+    int32_t s = (it0 - cg * spg) * S;
+    int32_t left = nstages;
     auto next = [&]() {   // the stage after (cg, s) into registers, nothing past the last
         s += S;
-        if (s >= s1) {
-            s = s0;
+        if (s >= V) {
+            s = 0;
             ++cg;
         }
-        if (cg < kGroups) load(cg, s);
+        if (--left > 0) load(cg, s);
     };
     if (nstages > 0) {
-        load(0, s0);
+        load(cg, s);
         stage(gram_lds);
         next();
     }
@@ -610,10 +623,12 @@ __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int
         if (part < KP) {
             // the operands of a step are read while the one before it multiplies
             constexpr int kSteps = K / (4 * KP);
-            double2 x[2], y[2][NTJ];
+            double2 x[2][NTI], y[2][NTJ];
             auto fetch = [&](int n) {
                 const int e = 4 * (part + n * KP);
-                x[n & 1] = src[oa + e];
+#pragma unroll
+                for (int u = 0; u < NTI; ++u)
+                    x[n & 1][u] = src[oa[u] + e];
 #pragma unroll
                 for (int q = 0; q < NTJ; ++q)
                     y[n & 1][q] = src[ob[q] + e];
@@ -622,30 +637,44 @@ __global__ void __launch_bounds__(256, 2) k_gram(const char* __restrict__ A, int
 #pragma unroll
             for (int n = 0; n < kSteps; ++n) {
                 if (n + 1 < kSteps) fetch(n + 1);
-                const double2 a = x[n & 1];
 #pragma unroll
-                for (int q = 0; q < NTJ; ++q) {
-                    const double2 b = y[n & 1][q];
-                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[q], 0, 0, 0);
-                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[q], 0, 0, 0);
-                    re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[q], 0, 0, 0);
-                    im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[q], 0, 0, 0);
+                for (int u = 0; u < NTI; ++u) {
+                    const double2 a = x[n & 1][u];
+#pragma unroll
+                    for (int q = 0; q < NTJ; ++q) {
+                        const double2 b = y[n & 1][q];
+                        re[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[u][q], 0, 0, 0);
+                        im[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[u][q], 0, 0, 0);
+                        re[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[u][q], 0, 0, 0);
+                        im[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[u][q], 0, 0, 0);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    if (part >= KP) return;
     const int NI = 16 * nti, NJ = 16 * NTJ;
-    double2* out = reinterpret_cast<double2*>(partials) + ((int64_t)blockIdx.x * KP + part) * NI * NJ;
+    // the wavefronts' parts of a tile meet in LDS, one after the other
+    double2* out = reinterpret_cast<double2*>(partials) + (int64_t)blockIdx.x * NI * NJ;
+#pragma unroll 1
+    for (int k = 0; k < KP; ++k) {
+        __syncthreads();
+        if (part != k) continue;
 #pragma unroll
-    for (int q = 0; q < NTJ; ++q) {
+        for (int u = 0; u < NTI; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = ti * 16 + 4 * r + kk;
-            const int j = q * 16 + t;
-            out[(int64_t)i * NJ + j] = make_double2(re[q][r], im[q][r]);
-        }
+            for (int q = 0; q < NTJ; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int e = ((ti + u) * 16 + 4 * r + kk) * NJ + q * 16 + t;
+                    double2 v = make_double2(re[u][q][r], im[u][q][r]);
+                    if (k > 0) {
+                        const double2 w = gram_lds[e];
+                        v = make_double2(w.x + v.x, w.y + v.y);
+                    }
+                    if (k < KP - 1) gram_lds[e] = v;
+                    else out[e] = v;
+                }
     }
 }
 
@@ -865,58 +894,58 @@ int gram_chunks(const ndq_geom* g, int na, int nb) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(4096, cap), (g->volume + 63) / 64));
 }
 
-// Wavefronts that share a row tile: all four for up to 16 rows, two for up to 32.
-int gram_kp(int na, int nw) {
+// Workgroups, each with a partial result of its own.  Up to 32 rows leave room for
+// four workgroups on a CU, three row tiles for two; 64 rows have no more than
+// 512 partial results anyway.
+int gram_wgs(int na, int nb, int nw) {
     const int nti = (na + 15) / 16;
-    int kp = nti == 1 ? 4 : nti == 2 ? 2 : 1;
-    while (kp > nw) kp >>= 1;
-    return kp;
+    return nti <= 2 ? std::min(nw, 1024) : nti == 3 && nb <= 48 ? std::min(nw, 512) : nw;
 }
 
-// A stage holds K elements of every row; a lane stages at most kGramLoads words
-// of A and of B, so K = 16 serves any block, and smaller blocks take longer
-// runs (16 S bytes of each field) with the fewer accumulators they need.
-template <int PB, int K, int NTJ, int KP>
-hipError_t launch_gram_kp(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
-                          double* partials, hipStream_t st) {
-    const int chunks = nw / KP;
-    int32_t spc = (V + chunks - 1) / chunks;
-    spc = (spc + 63) & ~63;   // whole stages, and runs that start on a cache line
-    const size_t lds = (size_t)2 * (na + nb) * (K + 1) * sizeof(double2);
+template <int PB, int K, int NTI, int NTJ, int KP>
+hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int wgs,
+                         double* partials, hipStream_t st) {
+    const size_t lds = std::max((size_t)2 * (na + nb) * (K + 1), (size_t)(16 * ((na + 15) / 16)) * (16 * NTJ)) *
+                       sizeof(double2);
     if (lds > 65536) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram<PB, K, NTJ, KP>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram<PB, K, NTI, NTJ, KP>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_gram<PB, K, NTJ, KP>), dim3(chunks), dim3(256), lds, st, A, na, B, nb, vb, vbB, V, spc,
+    hipLaunchKernelGGL((k_gram<PB, K, NTI, NTJ, KP>), dim3(wgs), dim3(256), lds, st, A, na, B, nb, vb, vbB, V,
                        partials);
     return hipGetLastError();
 }
 
-template <int PB, int K, int NTJ>
-hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
-                         double* partials, hipStream_t st) {
-    switch (gram_kp(na, nw)) {
-        case 4: return launch_gram_kp<PB, K, NTJ, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-        case 2: return launch_gram_kp<PB, K, NTJ, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-        default: return launch_gram_kp<PB, K, NTJ, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    }
-}
-
+// A stage holds K elements of every row; a lane stages at most kGramLoads words
+// of A and of B, so K = 16 serves any block, and smaller blocks take longer
+// runs (16 S bytes of each field) with the fewer accumulators they need.  Up to 4
+// rows fill their lanes only with K = 256: against K = 64, 2 fields on 24^3x48 306 ->
+// 269 us, on 8^3x16 19.4 -> 15.2 us (3 and 4 fields on 24^3x48 +3% and -6%); K = 128 for up
+// to 8 rows gains on small lattices alone and loses 4% on 24^3x48.
 template <int PB>
-hipError_t launch_gram(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int nw,
+hipError_t launch_gram(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int wgs,
                        double* partials, hipStream_t st) {
     static_assert(64 * 16 <= 256 * kGramLoads, "a stage of 64 rows");
-    const int ntj = (nb + 15) / 16;
-    if (na <= 16 && ntj == 1) return launch_gram_k<PB, 64, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    if (na <= 32 && ntj == 1) return launch_gram_k<PB, 32, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    if (na <= 32 && ntj == 2) return launch_gram_k<PB, 32, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    switch (ntj) {
-        case 1: return launch_gram_k<PB, 16, 1>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-        case 2: return launch_gram_k<PB, 16, 2>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-        case 3: return launch_gram_k<PB, 16, 3>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-        default: return launch_gram_k<PB, 16, 4>(A, na, B, nb, vb, vbB, V, nw, partials, st);
-    }
+    const int nti = (na + 15) / 16, ntj = (nb + 15) / 16;
+    auto go = [&](auto launch) { return launch(A, na, B, nb, vb, vbB, V, wgs, partials, st); };
+    if (na <= 4 && nb <= 4) return go(&launch_gram_k<PB, 256, 1, 1, 4>);
+    if (nti == 1 && ntj == 1) return go(&launch_gram_k<PB, 64, 1, 1, 4>);
+    if (nti == 2 && ntj == 1) return go(&launch_gram_k<PB, 32, 1, 1, 2>);
+    if (nti == 1 && ntj == 2) return go(&launch_gram_k<PB, 32, 1, 2, 4>);
+    if (nti == 2 && ntj == 2) return go(&launch_gram_k<PB, 32, 1, 2, 2>);
+    if (nti == 3 && ntj == 1) return go(&launch_gram_k<PB, 16, 3, 1, 4>);
+    if (nti == 3 && ntj == 2) return go(&launch_gram_k<PB, 16, 3, 2, 4>);
+    if (nti == 3 && ntj == 3) return go(&launch_gram_k<PB, 16, 3, 3, 4>);
+    if (ntj == 1) return go(&launch_gram_k<PB, 16, 1, 1, 1>);   // 4 row tiles
+    if (ntj == 2) return go(&launch_gram_k<PB, 16, 1, 2, 1>);
+    if (ntj == 3)
+        return nti == 1   ? go(&launch_gram_k<PB, 16, 1, 3, 4>)
+               : nti == 2 ? go(&launch_gram_k<PB, 16, 1, 3, 2>)
+                          : go(&launch_gram_k<PB, 16, 1, 3, 1>);
+    return nti == 1   ? go(&launch_gram_k<PB, 16, 1, 4, 4>)
+           : nti == 2 ? go(&launch_gram_k<PB, 16, 1, 4, 2>)
+                      : go(&launch_gram_k<PB, 16, 1, 4, 1>);   // 3 or 4 row tiles
 }
 }  // namespace
 
@@ -929,20 +958,18 @@ int gram_block(const ndq_geom* g, const void* A, int na, const ndq_spinor* B, do
                hipStream_t st) {
     const int nb = B->nrhs;
     if (na < 1 || nb < 1 || na > 64 || nb > 64) return fail(NDQ_EINVAL, "gram: block sizes must be in [1, 64]");
-    const int nw = gram_chunks(g, na, nb);
+    const int wgs = gram_wgs(na, nb, gram_chunks(g, na, nb));
     const int32_t V = (int32_t)g->volume;
     const int64_t vb = spinor_rhs_bytes(g, NDQ_F64, NDQ_FULL);
     const int64_t vbB = spinor_rhs_bytes(g, B->prec, NDQ_FULL);
     const char* a = static_cast<const char*>(A);
     const char* b = static_cast<const char*>(B->data);
     switch (B->prec) {
-        case NDQ_F64: NDQ_HIP(launch_gram<P64>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
-        case NDQ_F32: NDQ_HIP(launch_gram<P32>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
-        default: NDQ_HIP(launch_gram<P16>(a, na, b, nb, vb, vbB, V, nw, partials, st)); break;
+        case NDQ_F64: NDQ_HIP(launch_gram<P64>(a, na, b, nb, vb, vbB, V, wgs, partials, st)); break;
+        case NDQ_F32: NDQ_HIP(launch_gram<P32>(a, na, b, nb, vb, vbB, V, wgs, partials, st)); break;
+        default: NDQ_HIP(launch_gram<P16>(a, na, b, nb, vb, vbB, V, wgs, partials, st)); break;
     }
-    // partial tiles written: the kernel's chunks times the wavefronts sharing a row tile
-    const int kp = gram_kp(na, nw);
-    hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, nw / kp * kp, G);
+    hipLaunchKernelGGL(k_gram_reduce, dim3(na * nb), dim3(kBlock), 0, st, partials, na, nb, wgs, G);
     NDQ_HIP(hipGetLastError());
     return NDQ_OK;
 }

@@ -31,3 +31,19 @@ def test_gram_shapes(dims, na, nb):
     G = ndq.spinor_gram(g, A, B).cpu().numpy()
     ref = a.reshape(na, -1).conj() @ b.reshape(nb, -1).T
     assert np.abs(G - ref).max() <= 1e-13 * 12 * v
+
+
+@pytest.mark.parametrize("dims,na,nb", [((2, 2, 2, 2), 34, 3), ((6, 4, 10, 2), 48, 33), ((4, 6, 6, 10), 33, 20),
+                                        ((8, 16, 16, 16), 41, 40), ((2, 2, 2, 2), 2, 4), ((4, 6, 6, 10), 4, 1),
+                                        ((4, 6, 6, 10), 5, 8), ((8, 16, 16, 16), 3, 3), ((8, 16, 16, 16), 8, 2)])
+def test_gram_three_row_tiles_and_small_blocks(dims, na, nb):
+    v = geometry.volume(dims)
+    rng = np.random.default_rng(93)
+    a = rng.standard_normal((na, v, 4, 3)) + 1j * rng.standard_normal((na, v, 4, 3))
+    b = rng.standard_normal((nb, v, 4, 3)) + 1j * rng.standard_normal((nb, v, 4, 3))
+    g = ndq.Geometry(dims)
+    A = ndq.SpinorField.pack(g, torch.from_numpy(a).cuda(), ndq.F64, ndq.FULL)
+    B = ndq.SpinorField.pack(g, torch.from_numpy(b).cuda(), ndq.F64, ndq.FULL)
+    G = ndq.spinor_gram(g, A, B).cpu().numpy()
+    ref = a.reshape(na, -1).conj() @ b.reshape(nb, -1).T
+    assert np.abs(G - ref).max() <= 1e-13 * 12 * v
