@@ -326,6 +326,32 @@ template <> struct SpinorIO<P16> {
         }
         reinterpret_cast<float*>(v.base + (int64_t)48 * v.stride)[s] = amax;
     }
+    // plane j: components 4j to 4j + 3
+    __device__ static __forceinline__ void load_plane(const SpinorView& v, int64_t s, int j, C<R> x[4]) {
+        const uint4 w = (reinterpret_cast<const uint4*>(v.base) + s)[(int64_t)j * v.stride];
+        const float scale = reinterpret_cast<const float*>(v.base + (int64_t)48 * v.stride)[s];
+        const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&words[k]));
+            x[k] = {f.x * scale, f.y * scale};
+        }
+    }
+    // plane j of a site whose largest real is amax, the scale with plane 0; x becomes
+    // what a load returns
+    __device__ static __forceinline__ void store_plane(const SpinorView& v, int64_t s, int j, float amax, C<R> x[4]) {
+        const float inv = amax > 0.f ? 1.0f / amax : 0.f;
+        uint32_t words[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const __half2 h = __floats2half2_rn(x[k].r * inv, x[k].i * inv);
+            words[k] = *reinterpret_cast<const uint32_t*>(&h);
+            const float2 f = __half22float2(h);
+            x[k] = {f.x * amax, f.y * amax};
+        }
+        (reinterpret_cast<uint4*>(v.base) + s)[(int64_t)j * v.stride] = make_uint4(words[0], words[1], words[2], words[3]);
+        if (j == 0) reinterpret_cast<float*>(v.base + (int64_t)48 * v.stride)[s] = amax;
+    }
     // single complex component c: half2 (c & 3) of plane c >> 2, times the site's scale
     __device__ static __forceinline__ C<R> load_comp(const SpinorView& v, int64_t s, int c) {
         const uint32_t w = reinterpret_cast<const uint32_t*>(v.base)[4 * ((int64_t)(c >> 2) * v.stride + s) + (c & 3)];

@@ -319,8 +319,8 @@ __global__ void __launch_bounds__(BLOCK) k_wilson(WilsonArgs a) {
 // Epilogue of the direction split: the part of the 64 outputs that wavefront w
 // finishes, kN complex components from first(w).  F64: one spin component of
 // each site; F32: the two 16-byte planes 2w, 2w+1 (wavefronts 0..2), so that
-// every access is a full word; F16: the whole spinor (wavefront 0), because the
-// per-site scale needs all 24 reals.
+// every access is a full word; F16: plane w (wavefronts 0..2), whose stores wait
+// for the site's scale, the largest of all 24 reals.
 template <int SP> struct SplitPart;
 template <> struct SplitPart<P64> {
     static constexpr int kN = 3;
@@ -347,13 +347,10 @@ template <> struct SplitPart<P32> {
     }
 };
 template <> struct SplitPart<P16> {
-    static constexpr int kN = 12;
-    __device__ static __forceinline__ bool has(int w) { return w == 0; }
-    __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, int, C<float> x[kN]) {
-        SpinorIO<P16>::load(v, s, x);
-    }
-    __device__ static __forceinline__ void store(const SpinorView& v, int64_t s, int, const C<float> x[kN]) {
-        SpinorIO<P16>::store(v, s, x);
+    static constexpr int kN = 4;
+    __device__ static __forceinline__ bool has(int w) { return w < 3; }
+    __device__ static __forceinline__ void load(const SpinorView& v, int64_t s, int w, C<float> x[kN]) {
+        SpinorIO<P16>::load_plane(v, s, w, x);
     }
 };
 
@@ -372,6 +369,11 @@ template <> struct SplitPart<P16> {
 // between the arithmetic and the barrier instead: 12.4 ms, 72.1 us and
 // 349-389 ms, although that keeps 5 wavefronts per SIMD instead of 4).  NV = 0
 // serves launches without extra vectors, whose registers the loads would cost.
+// F16 shares the epilogue out by planes too and settles the site's scale with a
+// second barrier: a whole spinor and three whole extra vectors in wavefront 0 took
+// 160 registers in every wavefront, a plane of each takes 93 (5 wavefronts per SIMD
+// instead of 3; one F16 sign apply on 24^3x48 9.34 -> 7.51 ms, on 16^3x32 1.97 -> 1.64
+// ms, Q without extra vectors on 32^3x64 126 -> 121 us, the same bits).
 template <int SP, int LP, int RECON, bool NT, int NV>
 __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     using R = typename SpinorIO<SP>::R;
@@ -464,12 +466,13 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     if (y) vout.site0 = out1;
     __syncthreads();
     double red = 0.0;
-    if (active && Part::has(w)) {
+    const bool mine = active && Part::has(w);
+    C<R> t[Part::kN];
+    if (mine) {
         const R b = (R)b_d;
         const R as = (R)as_d;
         const R c0 = (R)coef(Coef{c0_f, c0_d});
         const int c1 = Part::kN * w;   // first component of this part
-        C<R> t[Part::kN];
 #pragma unroll
         for (int k = 0; k < Part::kN; ++k) {
             const int c = c1 + k;
@@ -487,10 +490,23 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
                 for (int k = 0; k < Part::kN; ++k) t[k] = {t[k].r + cr * vv[j][k].r, t[k].i + cr * vv[j][k].i};
             }
         }
+    }
+    float amax = 0.f;
+    if constexpr (SP == P16) {
+        __shared__ float amax_lds[3][64];
+        if (mine) {
+#pragma unroll
+            for (int k = 0; k < Part::kN; ++k) amax = fmaxf(amax, fmaxf(fabsf(t[k].r), fabsf(t[k].i)));
+            amax_lds[w][lane] = amax;
+        }
+        __syncthreads();
+        amax = fmaxf(amax_lds[0][lane], fmaxf(amax_lds[1][lane], amax_lds[2][lane]));
+    }
+    if (mine) {
         const int64_t so = (int64_t)vout.site0 + i;
-        Part::store(vout, so, w, t);
+        if constexpr (SP == P16) SpinorIO<P16>::store_plane(vout, so, w, amax, t);   // leaves in t what was stored
+        else Part::store(vout, so, w, t);
         if (partials) {
-            if constexpr (SP == P16) Part::load(vout, so, w, t);   // norm of what was stored (after F16 rounding)
 #pragma unroll
             for (int k = 0; k < Part::kN; ++k) red += (double)t[k].r * t[k].r + (double)t[k].i * t[k].i;
         }
