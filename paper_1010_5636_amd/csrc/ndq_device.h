@@ -156,7 +156,8 @@ struct HopSpinor {
 // accumulator takes scale * w by fma instead of w by add.  The multi-RHS kernel
 // kept the vector units busy all the time with every half converted and scaled
 // (1416 vector instructions per site and field): 12 fields on 24^3x48 366 us;
-// this way (1008) 348 us, bound by L2 misses like the F32 form.
+// this way (1008) 348 us (332 us since the kernel reads its arguments in one go),
+// bound by L2 misses like the F32 form.
 struct HopWeight16 {
     float scale;
     __device__ __forceinline__ C<float> acc(C<float> a, C<float> x) const {

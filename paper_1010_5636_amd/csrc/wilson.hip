@@ -136,17 +136,13 @@ __device__ __forceinline__ void hop_bwd(const S& s, const C<R> u[3][3], C<R> acc
     hop_bwd_acc<MU>(s.weight(), w0, w1, acc);
 }
 
-struct NoLoads {
-    __device__ __forceinline__ void operator()() const {}
-};
-
 // PAIR64: FP64 also issues both hops' loads together (the direction split with
 // 12- or 8-real links, where the registers this takes keep 3 wavefronts per SIMD).
 // `more` issues further loads behind those of the hops, before their arithmetic.
-template <int SP, int LP, int RECON, int MU, bool NT, bool PAIR64 = false, typename More = NoLoads>
+template <int SP, int LP, int RECON, int MU, bool NT, bool PAIR64, typename More>
 __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, const int32_t nb[8],
                                          const SpinorView& vin, C<typename SpinorIO<SP>::R> acc[12],
-                                         More more = More()) {
+                                         More more) {
     using R = typename SpinorIO<SP>::R;
     using F = LinkFmt<LP, RECON>;
     typename SpinorIO<SP>::Hop sf, sb;
@@ -807,8 +803,8 @@ hipError_t launch_mrhs_fmt(const WilsonArgs& a, const MrhsGrid& m, int link_nt, 
 // Measured, tile form -> march: 12 fields on 24^3x48, 12-real links, 640 -> 521 us;
 // on 32^3x64, 18-real links, 2110 -> 1868 us (L2 misses 12.9 -> 10.8 GB).  Tried
 // and not kept: the next slice's x1 neighbours in flight across the barrier
-// (spills); FP64 (its registers); F16 fields (375 us against 348 us: half the
-// traffic, and the tile form's three wavefronts per SIMD hide more).
+// (spills); FP64 (its registers); F16 fields (375 us against 332 us: half the
+// traffic, and the tile form's four wavefronts per SIMD hide more).
 template <int N, typename R>
 __device__ __forceinline__ void pin(C<R> (&x)[N]) {   // computed here, not sunk below the stores
 #pragma unroll
