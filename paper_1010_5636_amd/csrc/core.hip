@@ -247,14 +247,14 @@ void clear_launch_tuning(int sprec, int lprec, int recon) {
 // 16 1690 -> 1554 us; 24 fields, which 6 divides, 2257 us against 2371).
 // F16 fields (half the bytes per field) keep one group in tile order.
 //
-// The full Q on F32 fields marches along x0 (k_wilson_march) from 4 fields on
-// where its 64-site columns hold 4096 slices in all, 8 for each of the 512
-// workgroups it keeps resident: measured against the tile form at 12, 8 and 4
-// fields, 24^3x48 (31104, 20736, 10368 column slices) 0.83, 0.62, 0.87 of its
-// time, 16^3x32 (6144, 4096, 2048) 0.77, 0.60, 0.92, 12^3x24 (2016, 1344, 672)
-// 0.96, 0.77, 1.14.  3 fields leave a wavefront in four without one and gain
-// from 8192 on (10368: 0.89; 4320: 1.05), 5 fields (groups of 3 and 2) never
-// do (0.93 to 1.17).
+// The full Q on F32 fields marches along x0 (k_wilson_march) where its 64-site
+// columns hold enough slices for the 512 workgroups it keeps resident, in groups of
+// up to 4 fields.  March over tile form, by fields (column slices in all):
+//   6 (4096) 0.93, 8 (4096) 0.88, 9 (5280) 0.97, 12 (6144) 0.77; 24^3x48 6 (20736)
+//   0.92, 8 (20736) 0.62, 12 (31104) 0.83; below 4096 12^3x24 8 (1344) 1.05, 4 (672) 1.22;
+//   one group: 4 (4096) 1.02, (10368) 0.87; 3 (4096) 1.03, (10368) 0.87: from 8192 on;
+//   a last group with 2 wavefronts or 1 idle: 10 (5280) 1.09, (6144) 0.85; 11 (5280)
+//   1.09, (6144) 0.84: from 6144 on; 5 fields (groups of 3 and 2) 0.93 to 1.17: never.
 MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, int nrhs, int ny) {
     (void)lprec; (void)recon;
     MrhsShape s;
@@ -274,7 +274,8 @@ MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, in
     }
     if (sprec == P32 && ny == 2 && nrhs >= 3 && nrhs != 5) {
         const int64_t slices = 2 * (int64_t)((g.s0 + 63) / 64) * ((nrhs + 3) / 4) * g.n0;
-        if (slices >= (nrhs == 3 ? 8192 : 4096)) s.group_major = 3;
+        const int64_t least = nrhs <= 4 ? 8192 : nrhs > 8 && nrhs % 4 >= 2 ? 6144 : 4096;
+        if (slices >= least) s.group_major = 3;
     }
     return s;
 }

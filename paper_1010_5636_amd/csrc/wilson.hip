@@ -1178,9 +1178,14 @@ hipError_t launch_wilson(int sprec, int lprec, int recon, const WilsonArgs& args
 namespace {
 // Launches the march can take: full F32 fields, Q with the same field as stencil
 // input and same-site term, 0, 2 or 3 extra vectors, 32-bit byte offsets.
+// Extra vectors from 8 fields on: the march reads them after the barrier of a step,
+// the tile form has more wavefronts to hide that.  D_N on 24^3x48, every second launch
+// with 2 or 3 vectors, marching in all launches against the tile form in all: 3
+// fields 1.00 of its time, 6 1.03, 7 1.11, 8 0.92, 9 0.79, 12 0.93, although the
+// launches without vectors take 0.87 to 0.97.
 bool march_fits(const WilsonArgs& a, int sprec, int ny, int nrhs) {
     if (sprec != P32 || ny != 2 || a.p0 != 0 || !a.has_self || !a.gamma5 || a.b_hop != -0.5 || a.partials ||
-        a.nv == 1 || nrhs < 3 || (int64_t)a.g.vh * 32 >= INT32_MAX)
+        a.nv == 1 || nrhs < (a.nv > 0 ? 8 : 3) || (int64_t)a.g.vh * 32 >= INT32_MAX)
         return false;
     const int32_t stride = 2 * a.g.vh;
     for (int p = 0; p < 2; ++p) {

@@ -81,3 +81,10 @@ def test_march_with_extra_vectors(dims, nrhs, recon):
         ndq.apply_sign(g, U, ov, x, y)
         out.append(y.buf)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("recon", [18, 12])
+@pytest.mark.parametrize("dims,nrhs", [((6, 4, 4, 8), 8), ((10, 6, 10, 6), 11), ((2, 2, 4, 6), 9)])
+def test_march_with_extra_vectors_in_several_groups(dims, nrhs, recon):
+    """From 8 fields on launches with extra vectors march too; one field idle, none, and a group of three."""
+    test_march_with_extra_vectors(dims, nrhs, recon)
