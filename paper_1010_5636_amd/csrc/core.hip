@@ -237,46 +237,69 @@ void clear_launch_tuning(int sprec, int lprec, int recon) {
     }
 }
 
+namespace {
+// The smallest divisor c of the 64-site tiles of a slice with 64 c >= 2 s1 (two x1
+// rows), -1 where a slice is not whole tiles.
+int two_row_chunk(const GeomK& g) {
+    const int64_t per_slice = g.vh / g.n0;
+    if (g.n0 < 4 || per_slice * g.n0 != g.vh || per_slice % 64) return -1;
+    const int64_t S = per_slice / 64;
+    for (int64_t c = 1; c <= S; ++c)
+        if (S % c == 0 && 64 * c >= 2 * (int64_t)g.s1) return (int)c;
+    return -1;
+}
+
+// Where the full Q on F32 fields marches along x0 (k_wilson_march) by default.
+// A column is 64 lanes whatever the slice holds, so thin slices leave lanes idle:
+// 6 fields on 4096x2x2x2, 4 of 64 lanes at work, 12.4 us as tiles and 123 marching;
+// 24 on 256x4^3, half of the lanes, 1.7 times the tiles' time; from three quarters
+// on the march gains as it does on full columns.
+// What it saves are reads past the L2s.  Marching over tile form (an apply; a sign,
+// whose every second launch has extra vectors), by megabytes of input and output:
+//   24 fields 202 1.15; 1.12, 255 0.94; 0.95, 295 0.83; 0.95, 382 0.69; 0.92;
+//   40 fields 212 1.17, 246 1.04, 337 0.78; 12 fields 202 1.12; 1.12, 221 1.06; 1.01,
+//   269 0.85; 0.94; 7 fields 236 1.15, 258 0.83, 352 0.83; 4 fields 201 1.55, 276 0.77;
+//   3 fields 207 0.98, 302 0.82: from about the 256 MB of the last-level cache on.
+// Below it the tiles lose to the march where they are at their worst: a last group
+// at most half full (9 fields 166 MB 0.73 to 0.94, 13 fields 160 0.90; 0.89, 20
+// fields 212 1.04; 0.94); slices of several chunks (16^3x32: 6 fields 0.91, 8 0.83;
+// 0.95, but 7, with an idle wavefront in one group, 1.05, and 12 on 16^4 1.04; 1.12),
+// or, where the tiles run in index order, slices beyond an XCD's L2 (24x20^3 6 fields
+// 0.78, 12x20^3 12 fields 0.83; 0.96).
+// 5 fields (groups of 3 and 2) 0.93 to 1.17: never.
+bool march_by_default(const GeomK& g, int nrhs, int rg, int chunk) {
+    if (nrhs < 3 || nrhs == 5) return false;
+    const int64_t lanes = 64 * (((int64_t)g.s0 + 63) / 64);
+    if (4 * (int64_t)g.s0 < 3 * lanes) return false;
+    const int64_t bytes = 2 * 2 * (int64_t)g.vh * 96 * nrhs;
+    if (bytes >= 250000000) return true;
+    const int last = rg > 0 ? nrhs % rg : 0;
+    if (last > 0 && 2 * last <= rg && nrhs <= 20) return 5 * (int64_t)g.s0 >= 4 * lanes && bytes >= 160000000;
+    const bool far = chunk > 0 ? 64 * (int64_t)chunk < g.s0
+                               : 2 * 96 * (int64_t)(rg > 0 ? rg : nrhs) * g.s0 > (int64_t(4) << 20);
+    return far && (nrhs == 6 ? bytes >= 150000000 : nrhs >= 8 && nrhs % 4 == 0 && bytes >= 200000000);
+}
+}  // namespace
+
 // Defaults from a sweep of the work order on 24^3x48 and 32^3x64 (12 and 60
 // fields): blocks of 8 or more F32/F64 fields run in group-major order with 6
 // fields per workgroup, and the tiles in chunks spanning two x1 rows of the
-// slice (the smallest divisor c of the slice's tiles with 64 c >= 2 s1), so
-// that the neighbour spinors of nearby tiles are still in L2 when re-read.
+// slice (two_row_chunk), so that the neighbour spinors of nearby tiles are still
+// in L2 when re-read.
 // Where 8 divides the number of fields and 6 does not, 8 fields per workgroup:
 // no group is left with 2 fields or 4 (8 FP64 fields on 24^3x48 1048 -> 800 us,
 // 16 1690 -> 1554 us; 24 fields, which 6 divides, 2257 us against 2371).
 // F16 fields (half the bytes per field) keep one group in tile order.
-//
-// The full Q on F32 fields marches along x0 (k_wilson_march) where its 64-site
-// columns hold enough slices for the 512 workgroups it keeps resident, in groups of
-// up to 4 fields.  March over tile form, by fields (column slices in all):
-//   6 (4096) 0.93, 8 (4096) 0.88, 9 (5280) 0.97, 12 (6144) 0.77; 24^3x48 6 (20736)
-//   0.92, 8 (20736) 0.62, 12 (31104) 0.83; below 4096 12^3x24 8 (1344) 1.05, 4 (672) 1.22;
-//   one group: 4 (4096) 1.02, (10368) 0.87; 3 (4096) 1.03, (10368) 0.87: from 8192 on;
-//   a last group with 2 wavefronts or 1 idle: 10 (5280) 1.09, (6144) 0.85; 11 (5280)
-//   1.09, (6144) 0.84: from 6144 on; 5 fields (groups of 3 and 2) 0.93 to 1.17: never.
 MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, int nrhs, int ny) {
     (void)lprec; (void)recon;
     MrhsShape s;
+    const int chunk = two_row_chunk(g);
     if (nrhs >= 8 && sprec != P16) {
         s.rg = nrhs % 8 == 0 && nrhs % 6 != 0 ? 8 : 6;
         s.group_major = 1;
-        const int64_t per_slice = g.vh / g.n0;
-        if (g.n0 >= 4 && per_slice * g.n0 == g.vh && per_slice % 64 == 0) {
-            const int64_t S = per_slice / 64;
-            for (int64_t c = 1; c <= S; ++c) {
-                if (S % c == 0 && 64 * c >= 2 * (int64_t)g.s1) {
-                    s.chunk = (int)c;
-                    break;
-                }
-            }
-        }
+        s.chunk = chunk;
     }
-    if (sprec == P32 && ny == 2 && nrhs >= 3 && nrhs != 5) {
-        const int64_t slices = 2 * (int64_t)((g.s0 + 63) / 64) * ((nrhs + 3) / 4) * g.n0;
-        const int64_t least = nrhs <= 4 ? 8192 : nrhs > 8 && nrhs % 4 >= 2 ? 6144 : 4096;
-        if (slices >= least) s.group_major = 3;
-    }
+    if (sprec == P32 && ny == 2 && march_by_default(g, nrhs, s.rg, chunk)) s.group_major = 3;
     return s;
 }
 
