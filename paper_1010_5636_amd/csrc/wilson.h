@@ -73,6 +73,12 @@ struct Tuning {
 // 18/12/8); set by ndq_set_launch / ndq_set_launch_for (the autotuner).
 Tuning& tuning(int sprec, int lprec, int recon);
 int default_order(const GeomK& g, int sprec, int ny);
+// Slices per workgroup of the march along x0, for `columns` columns of n0 slices: the
+// smallest T that takes the fewest steps in all, rounds of `resident` workgroups times
+// T slices and the two extra loads at a segment's ends (24^3x48, 12 fields, resident
+// 512: T = 16, 521 us; 12: 541, 24: 566).  Asked on every launch, so it goes through
+// numbers of rounds, not through every T up to n0 (some ms of host time at n0 = 2^20).
+int march_slices(int n0, int64_t columns, int resident);
 // The shape of one lattice and number of output parities (1: dslash, 2: Q):
 // the autotuner's choice for that lattice if it made one, else the format's.
 Tuning launch_tuning(const GeomK& g, int sprec, int lprec, int recon, int ny);

@@ -993,24 +993,6 @@ __global__ void __launch_bounds__(256, 2) k_wilson_march(MarchArgs a) {
     }
 }
 
-// Slices per workgroup: the T that takes the fewest steps in all, rounds of
-// `resident` workgroups times T slices and the two extra loads at a segment's
-// ends (24^3x48, 12 fields, resident 512: T = 16, 521 us; 12: 541, 24: 566).
-int march_slices(const GeomK& g, int nrhs, int resident) {
-    const int64_t columns = 2 * (int64_t)((g.s0 + 63) / 64) * ((nrhs + 3) / 4);
-    int best = 1;
-    int64_t cost = INT64_MAX;
-    for (int T = 1; T <= g.n0; ++T) {
-        const int64_t wgs = columns * ((g.n0 + T - 1) / T);
-        const int64_t c = (wgs + resident - 1) / resident * (2 * T + 3);
-        if (c < cost) {
-            cost = c;
-            best = T;
-        }
-    }
-    return best;
-}
-
 template <int LP, int RECON>
 hipError_t launch_march(const WilsonArgs& a, int nrhs, hipStream_t st) {
     int dev = 0, cus = 0;
@@ -1034,7 +1016,7 @@ hipError_t launch_march(const WilsonArgs& a, int nrhs, hipStream_t st) {
     m.nrhs = nrhs;
     m.ngroups = (nrhs + 3) / 4;
     m.tiles = (a.g.s0 + 63) / 64;
-    m.T = march_slices(a.g, nrhs, 2 * cus);
+    m.T = march_slices(a.g.n0, 2 * (int64_t)m.tiles * m.ngroups, 2 * cus);
     m.nseg = (a.g.n0 + m.T - 1) / m.T;
     const dim3 grid(2u * (unsigned)m.tiles * (unsigned)m.nseg * (unsigned)m.ngroups);
     const size_t lds = (size_t)2 * 7 * StagedLinks<LP, RECON>::kWords * 64 * sizeof(uint32_t);
@@ -1275,6 +1257,26 @@ hipError_t launch_wilson_multi(int sprec, int lprec, int recon, const MultiArgs&
         case P16 * 1000 + P16 * 100 + 12: return launch_multi_fmt<P16, P16, 12>(a, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+int march_slices(int n0, int64_t columns, int resident) {
+    int best = n0;
+    int64_t cost = INT64_MAX;
+    // k rounds of `resident` workgroups hold seg segments of each column, so T is at
+    // least n0 / seg; no k rounds cost less than the slices shared out evenly and 3 k
+    for (int64_t k = (columns + resident - 1) / resident;; ++k) {
+        if (cost < INT64_MAX && (2 * columns * n0 + resident - 1) / resident + 3 * k > cost) break;
+        const int64_t seg = std::min<int64_t>(n0, k * resident / columns);
+        const int T = (int)((n0 + seg - 1) / seg);
+        const int64_t rounds = (columns * ((n0 + T - 1) / T) + resident - 1) / resident;
+        const int64_t c = rounds * (2 * (int64_t)T + 3);
+        if (c <= cost) {
+            cost = c;
+            best = T;
+        }
+        if (T == 1) break;
+    }
+    return best;
 }
 
 TileOrder make_order(int64_t tiles, int n0, int c) {
