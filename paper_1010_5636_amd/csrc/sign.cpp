@@ -231,7 +231,7 @@ int rational_apply(const ndq_geom* g, const ndq_gauge* U, double m, const Approx
             const void* g;
             int32_t dims[4];      // a freed and re-created geometry may reuse the address
             const void* links;
-            int32_t prec, lprec, recon, every, block, xcd;
+            int32_t prec, lprec, recon, every, block, xcd, order;
             double m;
             const void* r;
             const void* ws;
@@ -247,6 +247,7 @@ int rational_apply(const ndq_geom* g, const ndq_gauge* U, double m, const Approx
         head.every = every;
         head.block = tu.block;
         head.xcd = tu.xcd_remap;
+        head.order = tu.order;
         head.m = m;
         head.r = r.data;
         head.ws = sc.ms;
