@@ -541,8 +541,9 @@ int ndq_get_launch_lattice(const ndq_geom* g, int sprec, int lprec, int recon, i
  * for lattice g, links U, spinor precision sprec, nrhs >= 2 fields and ny
  * output parities (2: Q, 1: the even/odd hopping block): times `reps` applies
  * of the order in use and of each candidate (fields per workgroup nrhs,
- * nrhs/2, nrhs/3, 6, 4, 2; group- and tile-major; automatic, index-order and
- * two-x1-row tile chunks) on a block of fields in ws (at least
+ * nrhs/2, nrhs/3, 8, 6, 4, 2; group- and tile-major; automatic, index-order and
+ * two-x1-row tile chunks; and, where it may run, the march along x0) on a block
+ * of fields in ws (at least
  * ndq_autotune_mrhs_workspace_bytes(g, sprec, nrhs, ny) bytes), and records the
  * fastest, keeping the order in use unless another is more than 3% faster.
  * If the environment variable NDQ_TUNE_CACHE names a file, an entry for this
