@@ -548,7 +548,8 @@ int ndq_get_launch_lattice(const ndq_geom* g, int sprec, int lprec, int recon, i
  * fastest, keeping the order in use unless another is more than 3% faster.
  * If the environment variable NDQ_TUNE_CACHE names a file, an entry for this
  * key found there is applied without timing (cached = 1) and a new result is
- * appended to it (one text line per key).  Synchronises `stream`.
+ * appended to it (one text line per key, tagged with a version of the kernels:
+ * entries of another version are passed over).  Synchronises `stream`.
  * Errors: NDQ_EINVAL, NDQ_EPREC, NDQ_ENOMEM, NDQ_EHIP. */
 typedef struct {
     int32_t rg, group_major, chunk, xcd_remap, link_nt;   /* chosen order             */

@@ -82,6 +82,10 @@ struct Events {
 };
 
 // ---- the on-disk cache of multi-RHS work orders ----------------------------
+// Each line ends with the kernels' version: orders timed with other kernels (lines
+// with another number, or with none) say nothing about these and are passed over.
+// Raise it with every change that may move the fastest order of a key.
+constexpr int kOrdersVersion = 2;
 std::mutex g_cache_mu;
 
 const char* cache_path() {
@@ -98,10 +102,10 @@ bool cache_lookup(const ndq_geom* g, int sprec, int lprec, int recon, int nrhs, 
     char line[512];
     bool found = false;
     while (fgets(line, sizeof(line), f)) {
-        int d[4], sp, lp, rc, nr, y, rg, gm, ch, xcd, nt;
+        int d[4], sp, lp, rc, nr, y, rg, gm, ch, xcd, nt, version;
         double t;
-        if (sscanf(line, "mrhs %d %d %d %d %d %d %d %d %d %d %d %d %d %d %lf", &d[0], &d[1], &d[2], &d[3], &sp, &lp,
-                   &rc, &nr, &y, &rg, &gm, &ch, &xcd, &nt, &t) != 15)
+        if (sscanf(line, "mrhs %d %d %d %d %d %d %d %d %d %d %d %d %d %d %lf v%d", &d[0], &d[1], &d[2], &d[3], &sp, &lp,
+                   &rc, &nr, &y, &rg, &gm, &ch, &xcd, &nt, &t, &version) != 16 || version != kOrdersVersion)
             continue;
         if (d[0] == g->dims[0] && d[1] == g->dims[1] && d[2] == g->dims[2] && d[3] == g->dims[3] && sp == sprec &&
             lp == lprec && rc == recon && nr == nrhs && y == ny) {
@@ -124,8 +128,9 @@ void cache_store(const ndq_geom* g, int sprec, int lprec, int recon, int nrhs, i
     std::lock_guard<std::mutex> lock(g_cache_mu);
     FILE* f = fopen(path, "a");
     if (!f) return;
-    fprintf(f, "mrhs %d %d %d %d %d %d %d %d %d %d %d %d %d %d %.4f\n", g->dims[0], g->dims[1], g->dims[2], g->dims[3],
-            sprec, lprec, recon, nrhs, ny, s.rg, s.group_major, s.chunk, s.xcd_remap, s.link_nt, us);
+    fprintf(f, "mrhs %d %d %d %d %d %d %d %d %d %d %d %d %d %d %.4f v%d\n", g->dims[0], g->dims[1], g->dims[2],
+            g->dims[3], sprec, lprec, recon, nrhs, ny, s.rg, s.group_major, s.chunk, s.xcd_remap, s.link_nt, us,
+            kOrdersVersion);
     fclose(f);
 }
 
