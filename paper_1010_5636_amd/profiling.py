@@ -330,9 +330,11 @@ def _batch24(reps):
 
 
 # Work orders of the multi-RHS stencil compared by ``_orders32`` (fields per
-# workgroup, group-major, tile chunk): the default, the tuned orders and the
-# one-field-per-group extreme.
-ORDERS32 = [(0, 0, -1), (6, 1, 16), (4, 1, 16), (2, 1, 16), (1, 1, 16), (12, 0, 16)]
+# workgroup, group order as set_mrhs_launch takes it, tile chunk): all fields in one
+# group, the tuned tile orders, the one-field-per-group extreme, and the default (the
+# march along x0).
+ORDERS32 = [(0, 0, -1), (6, 1, 16), (4, 1, 16), (2, 1, 16), (1, 1, 16), (12, 0, 16), (6, 3, 16)]
+ORDERS32_DIMS = (64, 32, 32, 32)
 
 
 def _orders32(reps):
@@ -342,15 +344,14 @@ def _orders32(reps):
     import synthetic
     import paper_1010_5636_amd as ndq
     from paper_1010_5636_amd import ndq as nb
-    dims = (64, 32, 32, 32)
-    g = ndq.Geometry(dims)
-    U = ndq.GaugeField.pack(g, torch.from_numpy(synthetic.gauge_field(dims)).cuda(), ndq.F32, 18)
+    g = ndq.Geometry(ORDERS32_DIMS)
+    U = ndq.GaugeField.pack(g, torch.from_numpy(synthetic.gauge_field(ORDERS32_DIMS)).cuda(), ndq.F32, 18)
     x = ndq.SpinorField(g, ndq.F32, ndq.FULL, 12)
     gen = torch.Generator(device="cuda").manual_seed(1002)
     x.buf.view(torch.float32).normal_(generator=gen)   # in place: no copy kernel besides the calibration
     y = x.like()
     for rg, gm, ch in ORDERS32:
-        nb.set_mrhs_launch(g, ndq.F32, ndq.F32, 18, 12, 2, rg, bool(gm), ch, True, -1)
+        nb.set_mrhs_launch(g, ndq.F32, ndq.F32, 18, 12, 2, rg, gm, ch, True, -1)
         for _ in range(reps):
             ndq.apply_Q(g, U, -1.4, x, y)
         torch.cuda.synchronize()
