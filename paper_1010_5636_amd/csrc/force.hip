@@ -157,9 +157,10 @@ __global__ void __launch_bounds__(256) k_force(ForceArgs a) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) row[k] = f[k];
         __syncthreads();
-        double2* dst = reinterpret_cast<double2*>(a.force);
-        for (int e = threadIdx.x; e < nsites * 16; e += 256)
-            dst[(int64_t)site_lex[e >> 4] * 16 + (e & 15)] = out[(e >> 4) * kRow + (e & 15)];
+        // by doubles: the caller's array need not be aligned to more
+        for (int e = threadIdx.x; e < nsites * 32; e += 256)
+            a.force[(int64_t)site_lex[e >> 5] * 32 + (e & 31)] =
+                reinterpret_cast<const double*>(out + (e >> 5) * kRow)[e & 31];
         if (a.grad) __syncthreads();   // before the gradient takes the rows
     }
     if (a.grad) {
