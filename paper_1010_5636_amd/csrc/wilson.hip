@@ -174,6 +174,13 @@ __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, 
     }
 }
 
+// Values computed here, not sunk to where they are used.
+template <int N, typename R>
+__device__ __forceinline__ void pin(C<R> (&x)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(x[k].r), "+v"(x[k].i));
+}
+
 // The one-lane kernels (k_wilson, the multi-RHS tile and the march along x0) add
 // the hops of a site in one order: -0, +1, -1, +2, -2, +3, -3, +0.  The last is
 // the one a march along x0 has last, so that all of them round alike.
@@ -576,8 +583,9 @@ struct StagedLinks {
 // right-hand sides r0 .. r1-1.  The views address right-hand side 0;
 // right-hand side r sits r * rhs_bytes further.  has_self = false: no
 // same-site term.  Must be reached by all 256 threads of the workgroup (it
-// synchronises once).
-template <int SP, int LP, int RECON, bool NT>
+// synchronises once).  PIN: the sums of each two hops are formed before the next
+// two (see k_wilson_multi).
+template <int SP, int LP, int RECON, bool NT, bool PIN = false>
 __device__ __forceinline__ void mrhs_tile(const GeomK& g, const char* links, int p, int32_t tile,
                                           const SpinorView& in, const SpinorView& self, bool has_self,
                                           const SpinorView& out, double a_self, double b_hop, int gamma5, double c0d,
@@ -637,6 +645,7 @@ __device__ __forceinline__ void mrhs_tile(const GeomK& g, const char* links, int
             if (mf == 1) hop_fwd<1>(sf, u, acc);
             if (mf == 2) hop_fwd<2>(sf, u, acc);
             if (mf == 3) hop_fwd<3>(sf, u, acc);
+            if constexpr (PIN) pin(acc);
         }
         const R b = (R)b_hop;
         if (has_self) {
@@ -805,12 +814,6 @@ hipError_t launch_mrhs_fmt(const WilsonArgs& a, const MrhsGrid& m, int link_nt, 
 // and not kept: the next slice's x1 neighbours in flight across the barrier
 // (spills); FP64 (its registers); F16 fields (375 us against 332 us: half the
 // traffic, and the tile form's four wavefronts per SIMD hide more).
-template <int N, typename R>
-__device__ __forceinline__ void pin(C<R> (&x)[N]) {   // computed here, not sunk below the stores
-#pragma unroll
-    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(x[k].r), "+v"(x[k].i));
-}
-
 struct MarchArgs {
     GeomK g;
     const char* links;
@@ -1040,6 +1043,14 @@ hipError_t launch_march(const WilsonArgs& a, int nrhs, hipStream_t st) {
 // taking one contiguous chunk of tiles (chunks adjacent in the list go to
 // workgroups on the same XCD), and each tile runs mrhs_tile with the epilogue
 // of Q.
+//
+// Bound like the tiles by L2 misses and their latency.  With the epilogue's constants
+// known the compiler keeps the products of all eight hops of an F16 field in registers
+// and scales them at the end: 220 registers, two wavefronts per SIMD, 1 field on
+// 32^3x64 337 us.  Formed after every two hops (PIN), 117 registers and four: 222 us
+// (2 fields on 24^3x48 131 -> 88 us, 4 fields 170 -> 144; 12 fields on lattices below
+// 10^4 sites 12.7 -> 13.5).  The one-lane kernels and k_wilson_mrhs, at 104 to 164
+// registers, lose 1 to 3% by it.
 template <int SP, int LP, int RECON>
 __global__ void __launch_bounds__(256) k_wilson_multi(MultiArgs a) {
     extern __shared__ uint32_t lw[];
@@ -1054,8 +1065,8 @@ __global__ void __launch_bounds__(256) k_wilson_multi(MultiArgs a) {
         const int local = t - J.tile0;
         const int y = local / J.tiles;
         const int32_t tile = local - y * J.tiles;
-        mrhs_tile<SP, LP, RECON, false>(J.g, J.links, y, tile, J.in[y], J.self[y], true, J.out[y], J.a_self, -0.5, 1, 1.0,
-                                        0, J.nrhs, lw);
+        mrhs_tile<SP, LP, RECON, false, SP == P16>(J.g, J.links, y, tile, J.in[y], J.self[y], true, J.out[y], J.a_self,
+                                                   -0.5, 1, 1.0, 0, J.nrhs, lw);
         __syncthreads();   // the next tile overwrites the staged links
     }
 }
