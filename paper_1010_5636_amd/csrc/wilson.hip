@@ -372,6 +372,11 @@ template <> struct SplitPart<P16> {
 // between the arithmetic and the barrier instead: 12.4 ms, 72.1 us and
 // 349-389 ms, although that keeps 5 wavefronts per SIMD instead of 4).  NV = 0
 // serves launches without extra vectors, whose registers the loads would cost.
+// There FP64 fields with 8-real links load the same-site spinor after the barrier:
+// 166 registers instead of 178 keep three wavefronts per SIMD through the links'
+// decoding (24^3x48 Q 135.8 -> 122.5 us, dslash 71.7 -> 61.5, 32^3x64 dslash 223 -> 199).
+// 12-real links stay at two either way, and 18-real ones lose more by the later load
+// than a third wavefront gains (Q on 24^3x20 58.5 us, 63.8 with 140 registers).
 // F16 shares the epilogue out by planes too and settles the site's scale with a
 // second barrier: a whole spinor and three whole extra vectors in wavefront 0 took
 // 160 registers in every wavefront, a plane of each takes 93 (5 wavefronts per SIMD
@@ -437,10 +442,11 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
     Coef cj[NV > 0 ? NV : 1];
 #pragma unroll
     for (int j = 0; j < NV; ++j) cj[j] = a.cv[j];
+    constexpr bool kSelfLate = SP == P64 && RECON == 8 && NV == 0;
     C<R> sf[Part::kN], vv[NV > 0 ? NV : 1][Part::kN];
     // the epilogue's operands, in flight with those of the hops
     auto epilogue_loads = [&]() {
-        if (Part::has(w) && has_self) Part::load(vself, (int64_t)vself.site0 + i, w, sf);
+        if (!kSelfLate && Part::has(w) && has_self) Part::load(vself, (int64_t)vself.site0 + i, w, sf);
 #pragma unroll
         for (int j = 0; j < NV; ++j)
             if (Part::has(w) && j < nv) Part::load(vj[j], (int64_t)vj[j].site0 + i, w, vv[j]);
@@ -476,6 +482,7 @@ __global__ void __launch_bounds__(256) k_wilson_dirsplit(WilsonArgs a) {
         const R as = (R)as_d;
         const R c0 = (R)coef(Coef{c0_f, c0_d});
         const int c1 = Part::kN * w;   // first component of this part
+        if (kSelfLate && has_self) Part::load(vself, (int64_t)vself.site0 + i, w, sf);
 #pragma unroll
         for (int k = 0; k < Part::kN; ++k) {
             const int c = c1 + k;

@@ -73,3 +73,12 @@ F16_LINKS = [(1, 18), (1, 12), (1, 8), (2, 18), (2, 12)]
 def test_f16_fields_keep_four_wavefronts(kernels, name, lp, recon):
     for k, (registers, scratch) in of(kernels, name, 2, lp, recon).items():
         assert registers <= 128 and scratch == 0, (k, registers, scratch)
+
+
+@pytest.mark.parametrize("nt", [0, 1])
+def test_eight_fp64_reals_keep_three_wavefronts(kernels, nt):
+    """The direction split without extra vectors."""
+    got = [v for k, v in of(kernels, "k_wilson_dirsplit", 0, 0, 8).items() if f"Lb{nt}ELi0E" in k]
+    assert len(got) == 1
+    registers, scratch = got[0]
+    assert registers <= 168 and scratch == 0
