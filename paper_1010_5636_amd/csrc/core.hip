@@ -204,12 +204,16 @@ LaunchKey launch_key(const GeomK& g, int sprec, int lprec, int recon, int ny) {
 //   dslash: 24^3x48 F32 39.0 -> 36.1 us, F64 82.8 -> 81.6; 16^2x24x40 F32 16.4 -> 15.9.
 // A dslash keeps the index order where three slices of its input exceed the 4 MB
 // L2 of an XCD (32^3x64 F32 124 us, 129 chunked: every chunk re-reads its x1
-// borders from memory) and on lattices that the caches hold anyway (below 8 MB
-// of input; 16^3x32 F64 17.1 us, 17.7 chunked).
+// borders from memory) and on lattices that the caches hold anyway: below 8 MB of
+// input (16^3x32 F32 9.3 us, 10.0 chunked; 24^3x20, 12.7 MB, 17.3 us, 16.8 chunked),
+// FP64 below 16 MB (16^3x32, 12 MB, from HBM with 12-, 18- and 8-real links 16.1, 20.0
+// and 16.4 us, chunked 17.2, 20.6 and 17.6; 16^2x8x64 15.9, 16.7 chunked; 16^3x40, 15
+// MB, within 2%; 16^2x24x40, 22.5 MB, 28.1 us, 27.4 chunked).
 int default_order(const GeomK& g, int sprec, int ny) {
     if (ny == 2) return 1;
     const int64_t site = sprec == P64 ? 192 : sprec == P32 ? 96 : 52;
-    return (int64_t)g.vh * site >= (int64_t(8) << 20) && 3 * (int64_t)g.s0 * site <= (int64_t(4) << 20);
+    const int64_t least = (sprec == P64 ? int64_t(16) : int64_t(8)) << 20;
+    return (int64_t)g.vh * site >= least && 3 * (int64_t)g.s0 * site <= (int64_t(4) << 20);
 }
 
 Tuning launch_tuning(const GeomK& g, int sprec, int lprec, int recon, int ny) {
