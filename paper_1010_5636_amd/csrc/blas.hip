@@ -894,14 +894,21 @@ int gram_chunks(const ndq_geom* g, int na, int nb) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(4096, cap), (g->volume + 63) / 64));
 }
 
-// Workgroups, each with a partial result of its own.  Up to 32 rows leave room for
-// four workgroups on a CU, three row tiles for two; 64 rows have no more than
-// 512 partial results anyway.
+}  // namespace
+
+// Workgroups, each with a partial result of its own, of nw that the workspace holds:
+// as many as run at once, for up to 32 rows four on a CU, else two.  A few more
+// take a whole second round: 48 x 64 fields on 24^3x48 with the 682 that 32 MiB of
+// partial results hold 6.39 ms, with 512 4.00; 60 x 40 4.26 and 3.47, on 16^3x32 805
+// and 689 us; 64 x 32, 1024 against 512, 2.72 and 2.64 ms.  Up to 16 columns against 64
+// rows keep all 2048, whose loads hide each other's latency on large lattices: 60 x 2
+// on 24^3x48 1.46 ms, 1.57 with 512 (on 12^3x32 157 and 142 us).
 int gram_wgs(int na, int nb, int nw) {
     const int nti = (na + 15) / 16;
-    return nti <= 2 ? std::min(nw, 1024) : nti == 3 && nb <= 48 ? std::min(nw, 512) : nw;
+    return nti <= 2 ? std::min(nw, 1024) : nti == 3 || nb > 16 ? std::min(nw, 512) : nw;
 }
 
+namespace {
 template <int PB, int K, int NTI, int NTJ, int KP>
 hipError_t launch_gram_k(const char* A, int na, const char* B, int nb, int64_t vb, int64_t vbB, int32_t V, int wgs,
                          double* partials, hipStream_t st) {

@@ -108,6 +108,8 @@ int convert(const ndq_geom* g, const ndq_spinor* dst, const ndq_spinor* src, hip
 // full spinor fields (contiguous, na, nb <= 64), on the matrix cores; partials
 // needs gram_partials_bytes(g, na, nb).
 size_t gram_partials_bytes(const ndq_geom* g, int na, int nb);
+// its workgroups, at most the nw partial results of the workspace
+int gram_wgs(int na, int nb, int nw);
 int gram(const ndq_geom* g, const void* A, int na, const void* B, int nb, double* partials, double* G,
          hipStream_t st);
 int mode_dots(const ndq_geom* g, const void* modes, int nev, const ndq_spinor* v, double* partials,
