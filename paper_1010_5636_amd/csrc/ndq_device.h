@@ -347,7 +347,10 @@ template <> struct SpinorIO<P16> {
         for (int k = 0; k < 4; ++k) {
             const __half2 h = __floats2half2_rn(x[k].r * inv, x[k].i * inv);
             words[k] = *reinterpret_cast<const uint32_t*>(&h);
-            const float2 f = __half22float2(h);
+            // read back from the word that is stored: a second conversion of the product
+            // may be fused with it and round once where the stored one rounds twice
+            asm volatile("" : "+v"(words[k]));
+            const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&words[k]));
             x[k] = {f.x * amax, f.y * amax};
         }
         (reinterpret_cast<uint4*>(v.base) + s)[(int64_t)j * v.stride] = make_uint4(words[0], words[1], words[2], words[3]);
