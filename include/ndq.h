@@ -484,7 +484,9 @@ int ndq_set_launch_for(int sprec, int lprec, int recon, int block, int xcd_remap
  * must divide 8, else group-major is used): the XCDs walk the same tiles
  * together, sharing the links through the last-level cache; 3 walks the lattice
  * along x0 in columns of 64 sites, 4 fields per workgroup (full Q on F32 fields
- * with nrhs >= 3; elsewhere 3 means 1, and rg and chunk say how);
+ * with nrhs >= 3 and fewer than 2^26 sites a parity; launches that fuse further
+ * vectors, as the sign's recurrence does, with nrhs >= 8; elsewhere 3 means 1, and
+ * rg and chunk say how);
  * chunk: -1 automatic, 0 tiles in index order, c > 0 c consecutive tiles of
  * every time slice in turn (c must divide the 64-site tiles of a slice);
  * xcd_remap as in ndq_set_launch; link_nt: links loaded with the non-temporal

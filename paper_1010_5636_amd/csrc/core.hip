@@ -292,7 +292,11 @@ bool march_by_default(const GeomK& g, int nrhs, int rg, int chunk) {
 // in L2 when re-read.
 // Where 8 divides the number of fields and 6 does not, 8 fields per workgroup:
 // no group is left with 2 fields or 4 (8 FP64 fields on 24^3x48 1048 -> 800 us,
-// 16 1690 -> 1554 us; 24 fields, which 6 divides, 2257 us against 2371).
+// 16 1690 -> 1554 us; 24 fields, which 6 divides, 2257 us against 2371).  On 21
+// lattices, 12- and 18-real links, 8 against 6 per workgroup, mean and worst: FP64 Q
+// 8 fields 0.77, 0.92; 16 0.93, 1.07; 32 0.95, 1.00; 40 0.99, 1.05; dslash FP64 8 0.76,
+// 0.98; 16 0.88, 1.05; 32 0.91, 1.08; 40 0.97, 1.08; F32 8 0.81, 1.01; 16 0.91, 1.04; 32
+// 0.90, 1.02; 40 0.95, 1.02.
 // F16 fields (half the bytes per field) keep one group in tile order.
 MrhsShape default_mrhs_shape(const GeomK& g, int sprec, int lprec, int recon, int nrhs, int ny) {
     (void)lprec; (void)recon;

@@ -137,7 +137,7 @@ __device__ __forceinline__ void hop_bwd(const S& s, const C<R> u[3][3], C<R> acc
 }
 
 // PAIR64: FP64 also issues both hops' loads together (the direction split with
-// 12- or 8-real links, where the registers this takes keep 3 wavefronts per SIMD).
+// 12- or 8-real links; 18-real ones would take the registers of a wavefront).
 // `more` issues further loads behind those of the hops, before their arithmetic.
 template <int SP, int LP, int RECON, int MU, bool NT, bool PAIR64, typename More>
 __device__ __forceinline__ void hop_pair(const WilsonArgs& a, int p, int32_t i, const int32_t nb[8],
@@ -816,8 +816,9 @@ hipError_t launch_mrhs_fmt(const WilsonArgs& a, const MrhsGrid& m, int link_nt, 
 // k_wilson, so the results equal it bit for bit.  Outputs are stored with the
 // non-temporal hint: nothing in the launch reads them.  About 235 registers, two
 // wavefronts per SIMD.
-// Measured, tile form -> march: 12 fields on 24^3x48, 12-real links, 640 -> 521 us;
-// on 32^3x64, 18-real links, 2110 -> 1868 us (L2 misses 12.9 -> 10.8 GB).  Tried
+// Measured, tile form in its default order and in its fastest one -> march: 12 fields
+// on 24^3x48, 12-real links, 640 and 570 -> 521 us; on 32^3x64, 18-real links, 2110 ->
+// 1868 us (L2 misses 12.9 -> 10.8 GB), 12-real 2000 in the fastest -> 1759.  Tried
 // and not kept: the next slice's x1 neighbours in flight across the barrier
 // (spills); FP64 (its registers); F16 fields (375 us against 332 us: half the
 // traffic, and the tile form's four wavefronts per SIMD hide more).
