@@ -816,12 +816,14 @@ hipError_t launch_mrhs_fmt(const WilsonArgs& a, const MrhsGrid& m, int link_nt, 
 // k_wilson, so the results equal it bit for bit.  Outputs are stored with the
 // non-temporal hint: nothing in the launch reads them.  About 235 registers, two
 // wavefronts per SIMD.
-// Measured, tile form in its default order and in its fastest one -> march: 12 fields
-// on 24^3x48, 12-real links, 640 and 570 -> 521 us; on 32^3x64, 18-real links, 2110 ->
-// 1868 us (L2 misses 12.9 -> 10.8 GB), 12-real 2000 in the fastest -> 1759.  Tried
-// and not kept: the next slice's x1 neighbours in flight across the barrier
-// (spills); FP64 (its registers); F16 fields (375 us against 332 us: half the
-// traffic, and the tile form's four wavefronts per SIMD hide more).
+// Measured, tile form in its default order and in its fastest one -> march, 12 fields:
+// 24^3x48, 12-real links, 640 and 570 -> 521 us; 32^3x64, 12-real links, 2000 in the
+// fastest -> 1759, 18-real links 2180 (6 fields per workgroup, 10.1 GB of L2 misses) and
+// 2090 (12 fields, 13.5 GB) -> 1917 us (10.8 GB).  Launches that fuse
+// three vectors gain nothing from it: on 24^3x48 1026 us, 1028 in the default tile order,
+// 907 in the fastest.  Tried and not kept: the next slice's x1 neighbours in flight
+// across the barrier (spills); FP64 (its registers); F16 fields (375 us against 332 us:
+// half the traffic, and the tile form's four wavefronts per SIMD hide more).
 struct MarchArgs {
     GeomK g;
     const char* links;
@@ -1183,7 +1185,8 @@ namespace {
 // the tile form has more wavefronts to hide that.  D_N on 24^3x48, every second launch
 // with 2 or 3 vectors, marching in all launches against the tile form in all: 3
 // fields 1.00 of its time, 6 1.03, 7 1.11, 8 0.92, 9 0.79, 12 0.93, although the
-// launches without vectors take 0.87 to 0.97.
+// launches without vectors take 0.87 to 0.97.  (In the tiles' default order; the fastest
+// one, chunk -1, makes 12 fields on 24^3x48 573 + 907 us as tiles, 540 + 1026 marching.)
 bool march_fits(const WilsonArgs& a, int sprec, int ny, int nrhs) {
     if (sprec != P32 || ny != 2 || a.p0 != 0 || !a.has_self || !a.gamma5 || a.b_hop != -0.5 || a.partials ||
         a.nv == 1 || nrhs < (a.nv > 0 ? 8 : 3) || (int64_t)a.g.vh * 32 >= INT32_MAX)

@@ -2,7 +2,7 @@
 
     python -m paper_1010_5636_amd.profiling stats   <out.txt> <cmd> <label>=<trace_dir> ...
     python -m paper_1010_5636_amd.profiling traffic <out.json> <copy_bytes> <cmd> <block,xcd>=<fetch_dir>,<write_dir> ...
-    python -m paper_1010_5636_amd.profiling kernels <out.txt> <copy_bytes> <cmd> <trace_dir> <fetch_dir> <write_dir>
+    python -m paper_1010_5636_amd.profiling kernels <out.txt> <copy_bytes> <cmd> <trace_dir> <fetch_dir> <write_dir> [<l2_dir>]
     python -m paper_1010_5636_amd.profiling run <workload>[,<workload>...] [reps]
     python -m paper_1010_5636_amd.profiling dispatches <out.txt> <copy_bytes> <cmd> <pattern> <trace_dir> <counter>=<dir> ...
 
@@ -10,8 +10,9 @@
 profiler (``WORKLOADS`` below), each a few launches of the kernels it names,
 followed by a device copy of 512 MiB for the counter calibration.  ``kernels``
 joins one kernel-trace run and one FETCH_SIZE and one WRITE_SIZE run of the
-same command into a per-kernel table: average duration, and HBM bytes per
-dispatch (median) scaled by the calibration copy.
+same command (and one of TCC_HIT_sum and TCC_MISS_sum) into a per-kernel table:
+average duration, and HBM bytes per dispatch (median) scaled by the calibration
+copy (and what missed the L2s).
 
 ``stats`` condenses ``*kernel_stats.csv`` (from ``rocprofv3 --kernel-trace
 --stats``) of one or more runs into a short text table, one section per run.
@@ -167,7 +168,16 @@ def lookup(rec: dict, fmt: str, launch: dict):
     return None
 
 
-def kernels_text(trace_dir: str, fetch_dir: str, write_dir: str, copy_bytes: int, command: str) -> str:
+def _l2_columns(hit: dict, miss: dict, name: str) -> str:
+    """Medians over dispatches: megabytes of missed lines, and hits over all requests."""
+    if name not in hit or name not in miss:
+        return f"{'-':>11}{'-':>7}"
+    h, m = (sorted(c[name])[len(c[name]) // 2] for c in (hit, miss))
+    return f"{128e-6 * m:>11.1f}{h / max(1.0, h + m):>7.2f}"
+
+
+def kernels_text(trace_dir: str, fetch_dir: str, write_dir: str, copy_bytes: int, command: str,
+                 l2_dir: str = "") -> str:
     """Per-kernel time and HBM traffic of one workload (see the module docstring)."""
     stats = {r["name"]: r for r in kernel_stats(trace_dir)}
     fetch = counters(fetch_dir, "FETCH_SIZE")
@@ -177,11 +187,16 @@ def kernels_text(trace_dir: str, fetch_dir: str, write_dir: str, copy_bytes: int
     if not cf or not cw:
         raise RuntimeError("calibration copy kernel not found in the counter output")
     sf, sw = copy_bytes / cf, copy_bytes / cw
+    hit = counters(l2_dir, "TCC_HIT_sum") if l2_dir else {}
+    miss = counters(l2_dir, "TCC_MISS_sum") if l2_dir else {}
+    l2 = f"{'L2miss_MB':>11}{'L2hit':>7}" if l2_dir else ""
     lines = ["# rocprofv3 kernel time and HBM traffic per dispatch", f"# command: {command}",
              f"# kernel source hash: {kernel_hash()}",
              f"# counter scale from a {copy_bytes}-byte device copy: {sf:.2f} bytes per FETCH_SIZE unit, "
              f"{sw:.2f} per WRITE_SIZE unit", "",
-             f"{'calls':>7}{'avg_us':>11}{'fetch_MB':>11}{'write_MB':>11}{'GB/s':>9}  kernel"]
+             f"{'calls':>7}{'avg_us':>11}{'fetch_MB':>11}{'write_MB':>11}{'GB/s':>9}{l2}  kernel"]
+    if l2_dir:
+        lines.insert(-2, "# L2miss_MB: lines of 128 bytes that missed (TCC_MISS_sum); L2hit: share of hits")
     rows = sorted(stats.values(), key=lambda r: -r["calls"] * r["avg_ns"])
     for r in rows:
         f = fetch.get(r["name"])
@@ -189,8 +204,8 @@ def kernels_text(trace_dir: str, fetch_dir: str, write_dir: str, copy_bytes: int
         fb = sf * sorted(f)[len(f) // 2] if f else float("nan")
         wb = sw * sorted(w)[len(w) // 2] if w else float("nan")
         gbs = (fb + wb) / r["avg_ns"] if f and w else float("nan")
-        lines.append(f"{r['calls']:>7}{r['avg_ns'] / 1e3:>11.3f}{fb / 1e6:>11.3f}{wb / 1e6:>11.3f}{gbs:>9.1f}  "
-                     f"{r['name'][:120]}")
+        lines.append(f"{r['calls']:>7}{r['avg_ns'] / 1e3:>11.3f}{fb / 1e6:>11.3f}{wb / 1e6:>11.3f}{gbs:>9.1f}"
+                     f"{_l2_columns(hit, miss, r['name']) if l2_dir else ''}  {r['name'][:120]}")
     return "\n".join(lines) + "\n"
 
 
@@ -329,6 +344,32 @@ def _batch24(reps):
     _log("batch24: done")
 
 
+def _blocks24(reps):
+    """Q on 24^3 x 48 with 12-real links where the solver has them in FP64 and F16: one
+    FP64 field, a block of 12 F16 fields, the low-mode filter's 60 FP64 fields (each
+    kernel's dispatches in that order)."""
+    import torch
+    import synthetic
+    import paper_1010_5636_amd as ndq
+    dims = (48, 24, 24, 24)
+    g = ndq.Geometry(dims)
+    u = torch.from_numpy(synthetic.gauge_field(dims)).cuda()
+    one = torch.from_numpy(synthetic.spinor(g.volume)).cuda()
+    for prec, nrhs in ((ndq.F64, 1), (ndq.F16, 12), (ndq.F64, 60)):
+        U = ndq.GaugeField.pack(g, u, prec, 12)
+        x = ndq.SpinorField(g, prec, ndq.FULL, nrhs)
+        f = ndq.SpinorField.pack(g, one, prec, ndq.FULL)
+        n = f.buf.numel()
+        for r in range(nrhs):
+            x.buf[r * n:(r + 1) * n].copy_(f.buf)
+        y = x.like()
+        for _ in range(reps):
+            ndq.apply_Q(g, U, -1.4, x, y)
+        torch.cuda.synchronize()
+        _log(f"blocks24: precision {prec}, {nrhs} fields done")
+        del U, x, y
+
+
 # Work orders of the multi-RHS stencil compared by ``_orders32`` (fields per
 # workgroup, group order as set_mrhs_launch takes it, tile chunk): all fields in one
 # group, the tuned tile orders, the one-field-per-group extreme, and the default (the
@@ -359,7 +400,7 @@ def _orders32(reps):
 
 
 WORKLOADS = {"fullq24": _fullq24, "mrhs32": _mrhs32, "filter24": _filter24, "modes24": _modes24, "batch24": _batch24,
-             "orders32": _orders32}
+             "blocks24": _blocks24, "orders32": _orders32}
 
 
 def dispatches_text(trace_dir: str, pmc_dirs, copy_bytes: int, pattern: str, labels, command: str) -> str:
@@ -445,8 +486,8 @@ def main(argv):
     if len(argv) >= 2 and argv[0] == "run":
         sys.path.insert(0, ROOT)
         return run(argv[1].split(","), int(argv[2]) if len(argv) > 2 else 10)
-    if len(argv) == 7 and argv[0] == "kernels":
-        txt = kernels_text(argv[4], argv[5], argv[6], int(argv[2]), argv[3])
+    if len(argv) in (7, 8) and argv[0] == "kernels":
+        txt = kernels_text(argv[4], argv[5], argv[6], int(argv[2]), argv[3], argv[7] if len(argv) == 8 else "")
         with open(argv[1], "w") as fh:
             fh.write(txt)
         print(txt)
